@@ -170,12 +170,13 @@ lgt_status lgt_create(const lgt_geom* geom, void* hip_stream, lgt_ctx** out) {
     c->V = V;
     c->vh = (int)(V / 2);
     c->g.vh = c->vh;
+    c->g.vs = c->vs = plane_stride(c->vh);
     c->g.bc = geom->fermion_t_bc;
     c->g.hop_ns = 0;
     c->g.hop_order = 0;
     c->stream = (hipStream_t)hip_stream;
     LGT_HIP(hipGetDevice(&c->device));
-    LGT_HIP(hipMalloc(&c->U64, (size_t)72 * c->vh * sizeof(double2)));
+    LGT_HIP(hipMalloc(&c->U64, (size_t)72 * c->vs * sizeof(double2)));
     LGT_HIP(hipMalloc(&c->state, sizeof(SolverState)));
     LGT_HIP(hipMalloc(&c->partials, (size_t)reduce_capacity(c->vh) * 4 * sizeof(double)));
     LGT_HIP(hipMalloc(&c->result, 64 * sizeof(double)));
@@ -425,8 +426,8 @@ static lgt_status md_run(lgt_ctx* c, void* U, void* P, const void* phi, double b
     double2* u0 = dH ? c->g64(kU0) : nullptr;
     double2* p0 = dH ? c->g64(kP0) : nullptr;
     if (dH) {
-      LGT_HIP(launch_copy64(72 * c->vh, thin, u0, c->stream));
-      LGT_HIP(launch_copy64(72 * c->vh, c->P64, p0, c->stream));
+      LGT_HIP(launch_copy64(72 * c->vs, thin, u0, c->stream));
+      LGT_HIP(launch_copy64(72 * c->vs, c->P64, p0, c->stream));
     }
 
     // plain (or even/odd-preconditioned) pseudofermion force kick at the thin links

@@ -68,7 +68,7 @@ static BatchWork* batch_work(lgt_ctx* c, int nr) {
   BatchWork* w = new BatchWork();
   c->batch = w;
   w->nr = nr;
-  const size_t full = (size_t)24 * c->vh * nr, half = (size_t)12 * c->vh * nr;
+  const size_t full = (size_t)24 * c->vs * nr, half = (size_t)12 * c->vs * nr;
   w->f.assign(12, nullptr);
   for (auto& p : w->f) {
     LGT_HIP(hipMalloc(&p, full * sizeof(double2)));
@@ -165,7 +165,7 @@ struct BatchSolver {
   Reduce red() const { return Reduce{w->partials, c->result, 0, w->npart, c->mbox_dev}; }
   template <typename R>
   int gsize() const { return w->G[sizeof(R) == 8 ? 1 : 0]; }
-  size_t halfn() const { return (size_t)12 * c->vh * nr; }
+  size_t halfn() const { return (size_t)12 * c->vs * nr; }
   double* vec(int slot) const { return w->dvec + slot * kMaxRhs; }
   double2* F(int i) const { return w->f[i]; }
 
@@ -224,7 +224,7 @@ struct BatchSolver {
     // x += alpha p moves to the direction update, which reads p anyway
     LGT_HIP((launch_mhop_schur_cg<R, !DAG>(c->g, nr, gsize<R>(), h4, wv, nullptr, r, p, vec(vMK2), w->st, red(),
                                             c->stream)));
-    LGT_HIP(launch_mxpay<R>(c->vh, nr, r, p, x, w->st, c->stream));
+    LGT_HIP(launch_mxpay<R>(c->vs, nr, r, p, x, w->st, c->stream));
   }
 
   void cg64(bool dag, double2* z, const double2* rhs, double tol) {
@@ -233,7 +233,7 @@ struct BatchSolver {
     double2* r = F(bW2) + n;
     double2* p = F(bW3) + n;
     double2* wv = F(bW4) + n;
-    LGT_HIP(launch_mcg_init64(c->vh, nr, rhs, r, p, z, w->st, red(), tol, o.max_iter, c->stream));
+    LGT_HIP(launch_mcg_init64(c->vh, c->vs, nr, rhs, r, p, z, w->st, red(), tol, o.max_iter, c->stream));
     for (int iter0 = 0;;) {
       c->drive(iter0, [&] {
         if (dag) iteration<double, true>(c->U64, t, wv, z, r, p);
@@ -266,7 +266,7 @@ struct BatchSolver {
     if (first) c->compress_links();
     LGT_HIP(launch_zero64((int)n, z, c->stream));
     LGT_HIP(launch_zero32((int)n, xs, c->stream));
-    LGT_HIP(launch_mnorm<double>(c->vh, 12, nr, rhs, red(), c->stream));
+    LGT_HIP(launch_mnorm<double>(c->vh, c->vs, 12, nr, rhs, red(), c->stream));
     read_results(nr);
     if (first) {
       const bool two_row = c->host_flags[1] == 0 && gsize<float>() > 0;
@@ -298,7 +298,7 @@ struct BatchSolver {
     s.all_done = std::all_of(verified.begin(), verified.end(), [](int v) { return v != 0; });
     upload_vecs();
     LGT_HIP(hipMemcpyAsync(w->dint, w->hint, kMaxRhs * sizeof(int), hipMemcpyHostToDevice, c->stream));
-    LGT_HIP(launch_mrescale(c->vh, nr, rhs, vec(vSigma), rs, ps, w->dint, vec(vPscale), c->stream));
+    LGT_HIP(launch_mrescale(c->vs, nr, rhs, vec(vSigma), rs, ps, w->dint, vec(vPscale), c->stream));
     write_state();
     while (!s.all_done) {
       c->drive(s.iter, [&] {
@@ -323,10 +323,10 @@ struct BatchSolver {
         w->hvec[vUnverified * kMaxRhs + k] = verified[k] ? 0.0 : 1.0;
       }
       upload_vecs();
-      LGT_HIP(launch_mmixed_update(c->vh, nr, xs, z, vec(vScale), c->stream));
+      LGT_HIP(launch_mmixed_update(c->vs, nr, xs, z, vec(vScale), c->stream));
       apply_normal64(dag, z, r64, vec(vUnverified));
       LGT_HIP(launch_xmy64((int)n, rhs, r64, c->stream));
-      LGT_HIP(launch_mnorm<double>(c->vh, 12, nr, r64, red(), c->stream));
+      LGT_HIP(launch_mnorm<double>(c->vh, c->vs, 12, nr, r64, red(), c->stream));
       read_results(nr);
       bool all = true;
       for (int k = 0; k < nr; ++k) {
@@ -362,7 +362,7 @@ struct BatchSolver {
       if (s.all_done) break;
       upload_vecs();
       LGT_HIP(hipMemcpyAsync(w->dint, w->hint, kMaxRhs * sizeof(int), hipMemcpyHostToDevice, c->stream));
-      LGT_HIP(launch_mrescale(c->vh, nr, r64, vec(vSigma), rs, ps, w->dint, vec(vPscale), c->stream));
+      LGT_HIP(launch_mrescale(c->vs, nr, r64, vec(vSigma), rs, ps, w->dint, vec(vPscale), c->stream));
       write_state();
     }
     // each right-hand side's count is the iterations its own recursion ran
@@ -415,7 +415,7 @@ struct BatchSolver {
     }
     upload_vecs();
     const double2* phi = F(bPhi);
-    LGT_HIP(launch_mnorm<double>(c->vh, 24, nr, phi, red(), c->stream));
+    LGT_HIP(launch_mnorm<double>(c->vh, c->vs, 24, nr, phi, red(), c->stream));
     read_results(nr);
     std::vector<double> pp(c->host_result, c->host_result + nr);
     for (double v : pp)
@@ -447,7 +447,7 @@ struct BatchSolver {
       // (the single solve's rule, correction_tol); the right-hand sides that
       // already meet the target get a zero residual, so their CG stops at
       // once and their solution stays as it is
-      LGT_HIP(launch_mzero_rhs(c->vh, 24, nr, F(bRes), finished, c->stream));
+      LGT_HIP(launch_mzero_rhs(c->vs, 24, nr, F(bRes), finished, c->stream));
       solve_M(true, F(bYtmp), F(bRes), tol_corr);
       solve_M(false, F(bE), F(bYtmp), tol_corr);
       LGT_HIP(launch_axpy64((int)nfull, 1.0, F(bE), F(bX), c->stream));
@@ -496,7 +496,7 @@ void lgt_ctx::dslash_batch(int nr, const double* kappas, const void* const* ins,
   const double* one = w->dvec + vOne * kMaxRhs;
   const double* mkap = w->dvec + vMKap * kMaxRhs;
   for (int k = 0; k < nr; ++k) LGT_HIP(launch_mpack(g, nr, k, (const double2*)ins[k], w->f[bPhi], stream));
-  const size_t h = (size_t)12 * vh * nr;
+  const size_t h = (size_t)12 * vs * nr;
   const Reduce red{w->partials, result, 0, w->npart, nullptr};
   if (f32) {
     // the half fields h[0], h[1] hold the even and odd FP32 input, h[2], h[3] the output
@@ -510,8 +510,8 @@ void lgt_ctx::dslash_batch(int nr, const double* kappas, const void* const* ins,
       LGT_HIP((launch_mhop_axpy<float, false>(g, nr, G, -1, hin, w->h[2], w->h[3], w->h[0], w->h[1], mkap, stream,
                                                nullptr, nullptr, red)));
     LGT_HIP(launch_zero64((int)(2 * h), w->f[bX], stream));
-    LGT_HIP(launch_mmixed_update(vh, nr, w->h[2], w->f[bX], one, stream));
-    LGT_HIP(launch_mmixed_update(vh, nr, w->h[3], w->f[bX] + h, one, stream));
+    LGT_HIP(launch_mmixed_update(vs, nr, w->h[2], w->f[bX], one, stream));
+    LGT_HIP(launch_mmixed_update(vs, nr, w->h[3], w->f[bX] + h, one, stream));
   } else {
     HopIn<double> hin{U64, w->f[bPhi], w->f[bPhi] + h};
     if (dag)
@@ -529,7 +529,7 @@ double lgt_ctx::bench_mhop(int nr, bool f32, const void* psi, int nrep) {
   tune_group_size(this, w, nr, f32);
   const int G = w->G[f32 ? 0 : 1];
   for (int k = 0; k < nr; ++k) LGT_HIP(launch_mpack(g, nr, k, (const double2*)psi, w->f[bPhi], stream));
-  const size_t h = (size_t)12 * vh * nr;
+  const size_t h = (size_t)12 * vs * nr;
   for (int k = 0; k < kMaxRhs; ++k) w->hvec[vOne * kMaxRhs + k] = 1.0;
   LGT_HIP(hipMemcpyAsync(w->dvec, w->hvec, 8 * kMaxRhs * sizeof(double), hipMemcpyHostToDevice, stream));
   const double* one = w->dvec + vOne * kMaxRhs;

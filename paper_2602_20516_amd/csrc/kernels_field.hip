@@ -14,6 +14,34 @@
 
 namespace lgt {
 
+// A packed field is 6 to 36 planes of one complex number per site, and a wave
+// reads the same sites of every plane at once.  On lattices past the caches
+// whose planes are a large power of two apart (8 MB at 32^3x64 in FP32) those
+// reads crowd onto a part of the memory channels: a plain sum over 24 float2
+// planes runs at 5.35 TB/s with planes 2^21 elements apart and at 6.2 TB/s
+// with them a little off that distance; the two-row hops at 32^3x64 take 125
+// (FP32) and 264 us (FP64) dense, 120 and 248 us padded, the smeared force
+// there 218.7 and 209.6 ms.  Planes of more than 131072 sites that are a
+// multiple of 16384 are therefore 2112 = 33 * 64 sites further apart (64,
+// 1088 and 4160 measured within 1 %).  Others stay dense: at 24^3x48 (81 *
+// 2^12 sites) the padding gave the FP64 hop 4 % and cost the smearing 0.6 %,
+// and fields that stay in the caches (16^4 and below) gain nothing.  A lattice
+// that only fits the 32-bit field offsets without the padding (for 1..16
+// batched fields, or the gauge field of the 32-site hop blocks) stays dense
+// too, so that no call is lost to it.
+constexpr int kPadMinVh = 131072;
+constexpr int kPadAlign = 16384;
+constexpr int kPadSites = 2112;
+int plane_stride(int vh) {
+  if (vh <= kPadMinVh || vh % kPadAlign != 0) return vh;
+  const int vs = vh + kPadSites;
+  const size_t lim = (size_t)1 << 32, e = sizeof(double2);
+  for (size_t n = 1; n <= 16; ++n)
+    if (12 * n * vh * e < lim && 12 * n * vs * e >= lim) return vh;
+  if ((size_t)72 * vh * e < lim && (size_t)72 * vs * e >= lim) return vh;
+  return vs;
+}
+
 constexpr int kPackSites = 64;  // lexicographic sites per pack block (32 per parity)
 
 template <int NC, bool W32>
@@ -48,7 +76,7 @@ __global__ __launch_bounds__(256) void k_pack(Geom g, const double2* __restrict_
     // of the two sites s0+2j, s0+2j+1 (same cb index) pick the one of parity p
     const int site = (par[2 * j] == p) ? 2 * j : 2 * j + 1;
     const double2 v = tile[k][site];
-    const size_t o = ((size_t)p * NC + k) * g.vh + cb0 + j;
+    const size_t o = ((size_t)p * NC + k) * g.vs + cb0 + j;
     out64[o] = v;
     if (W32) out32[o] = make_float2((float)v.x, (float)v.y);
   }
@@ -76,7 +104,7 @@ __global__ __launch_bounds__(256) void k_unpack(Geom g, const double2* __restric
     const int j = e % half;
     if (2 * j >= nsite) continue;
     const int site = (par[2 * j] == p) ? 2 * j : 2 * j + 1;
-    tile[k][site] = packed[((size_t)p * NC + k) * g.vh + cb0 + j];
+    tile[k][site] = packed[((size_t)p * NC + k) * g.vs + cb0 + j];
   }
   __syncthreads();
   for (int e = threadIdx.x; e < nsite * NC; e += 256) canon[(size_t)s0 * NC + e] = tile[e % NC][e / NC];
@@ -388,7 +416,7 @@ hipError_t launch_convert_64_32(int n, const double2* x, float2* y, hipStream_t 
   return hipGetLastError();
 }
 
-// Two-row copy of a packed link field ([2][4][9][vh] -> [2][4][6][vh]) and
+// Two-row copy of a packed link field ([2][4][9][vs] -> [2][4][6][vs]) and
 // the check that the links are SU(3): flag is set when a stored third row
 // differs from the conjugate cross product of the first two by more than tol
 // (per component, |re| + |im|), or is not finite.
@@ -397,18 +425,18 @@ hipError_t launch_convert_64_32(int n, const double2* x, float2* y, hipStream_t 
 constexpr double kTwoRowTol64 = 1e-14;
 
 template <typename R>
-__global__ __launch_bounds__(256) void k_compress_links(int vh, const R2<R>* __restrict__ U, R2<R>* __restrict__ Uc,
+__global__ __launch_bounds__(256) void k_compress_links(int vh, int vs, const R2<R>* __restrict__ U, R2<R>* __restrict__ Uc,
                                                         int* flag, R tol) {
   const int t = blockIdx.x * 256 + threadIdx.x;  // link (parity, mu) slowest, site fastest
   if (t >= 8 * vh) return;
   const int pm = t / vh, cb = t - pm * vh;
-  const R2<R>* src = U + (size_t)pm * 9 * vh + cb;
-  R2<R>* dst = Uc + (size_t)pm * 6 * vh + cb;
+  const R2<R>* src = U + (size_t)pm * 9 * vs + cb;
+  R2<R>* dst = Uc + (size_t)pm * 6 * vs + cb;
   C<R> m[9];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) m[k] = ld<R>(src + (size_t)k * vh);
+  for (int k = 0; k < 9; ++k) m[k] = ld<R>(src + (size_t)k * vs);
 #pragma unroll
-  for (int k = 0; k < 6; ++k) st<R>(dst + (size_t)k * vh, m[k]);
+  for (int k = 0; k < 6; ++k) st<R>(dst + (size_t)k * vs, m[k]);
   const C<R> r6 = conj(m[1] * m[5] - m[2] * m[4]);
   const C<R> r7 = conj(m[2] * m[3] - m[0] * m[5]);
   const C<R> r8 = conj(m[0] * m[4] - m[1] * m[3]);
@@ -418,12 +446,12 @@ __global__ __launch_bounds__(256) void k_compress_links(int vh, const R2<R>* __r
   if (!(dev <= tol)) *flag = 1;  // also for NaN
 }
 hipError_t launch_compress_links(const Geom& g, const float2* U32, float2* Uc, int* flag, hipStream_t s) {
-  hipLaunchKernelGGL(k_compress_links<float>, dim3((8 * g.vh + 255) / 256), dim3(256), 0, s, g.vh, U32, Uc, flag,
+  hipLaunchKernelGGL(k_compress_links<float>, dim3((8 * g.vh + 255) / 256), dim3(256), 0, s, g.vh, g.vs, U32, Uc, flag,
                      1e-5f);
   return hipGetLastError();
 }
 hipError_t launch_compress_links(const Geom& g, const double2* U64, double2* Uc, int* flag, hipStream_t s) {
-  hipLaunchKernelGGL(k_compress_links<double>, dim3((8 * g.vh + 255) / 256), dim3(256), 0, s, g.vh, U64, Uc, flag,
+  hipLaunchKernelGGL(k_compress_links<double>, dim3((8 * g.vh + 255) / 256), dim3(256), 0, s, g.vh, g.vs, U64, Uc, flag,
                      kTwoRowTol64);
   return hipGetLastError();
 }

@@ -62,7 +62,7 @@ __device__ __forceinline__ void emit_block(const Geom& g, double2* out, int p, i
       const int cb = blk * kSB + lane;
 #pragma unroll
       for (int k = 0; k < 9; ++k) {
-        double2* q = out + ((size_t)(p * 4 + mu) * 9 + k) * g.vh + cb;
+        double2* q = out + ((size_t)(p * 4 + mu) * 9 + k) * g.vs + cb;
         if (mode == 2) st<double>(q, ld<double>(q) - dt * M.m[k]);
         else st_nt2(q, M.m[k].re, M.m[k].im);
       }
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void k_bilinear_sb(Geom g, const double2* __re
   const int cb = blk * kSB + lane;
   const bool active = cb < g.vh;
   const int vh = g.vh;
-  const size_t half = (size_t)12 * vh;
+  const size_t half = (size_t)12 * g.vs;
   {  // element e = (field, component, site) of the 2 x 12 x 64 own-site values; sites past vh read zero
     const double2* ap = a + p * half;
     const double2* bp = b + p * half;
@@ -168,14 +168,14 @@ __global__ __launch_bounds__(256) void k_bilinear_sb(Geom g, const double2* __re
       const int f = e / (12 * kSB), k = (e % (12 * kSB)) / kSB, l = e % kSB;
       const int site = blk * kSB + l;
       double2 v = make_double2(0.0, 0.0);
-      if (site < vh) v = (f ? bp : ap)[(size_t)k * vh + site];
+      if (site < vh) v = (f ? bp : ap)[(size_t)k * g.vs + site];
       (f ? sb : sa)[k][l] = v;
     }
   }
   int c[4];
   cb_coords(g, p, active ? cb : 0, c);
   const int nf = cb_shift(g, c, mu, +1);
-  const unsigned ks = (unsigned)vh * (unsigned)sizeof(double2);
+  const unsigned ks = (unsigned)g.vs * (unsigned)sizeof(double2);
   const SpinorIn<double, double2> a_nb{make_rsrc(a + (1 - p) * half, (size_t)12 * ks), ks, 1u};
   const SpinorIn<double, double2> b_nb{make_rsrc(b + (1 - p) * half, (size_t)12 * ks), ks, 1u};
   __syncthreads();
@@ -195,10 +195,10 @@ __global__ __launch_bounds__(256) void k_bilinear_sb(Geom g, const double2* __re
     // each link is read once here: streamed past the caches (non-temporal)
     // so that the neighbour spinors stay in them
     M3<double> Ux;
-    const BufRsrc ru = make_rsrc(gptr<double>(U, g, p, mu), (size_t)9 * vh * sizeof(double2));
+    const BufRsrc ru = make_rsrc(gptr<double>(U, g, p, mu), (size_t)9 * g.vs * sizeof(double2));
 #pragma unroll
     for (int k = 0; k < 9; ++k)
-      Ux.m[k] = ld_buf_nt<double>(ru, (unsigned)cbx * (unsigned)sizeof(double2), (unsigned)(k * vh * sizeof(double2)));
+      Ux.m[k] = ld_buf_nt<double>(ru, (unsigned)cbx * (unsigned)sizeof(double2), (unsigned)(k * g.vs * sizeof(double2)));
     M = mscale(0.5 * coeff * kappa * sbc, proj_ta(mmul(Ux, Z)));
   }
   if (LAYOUT == kCanonical) __syncthreads();  // every wave is done with sa, sb before sh overwrites them
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void k_gauge_force_sb(Geom g, const double2* _
   if (mode == 1) {
     M = mscale(-beta / 3.0, mdag(A));
   } else {
-    const M3<double> Ux = load_m3<double>(gptr<double>(U, g, p, mu), g.vh, active ? cb : 0);
+    const M3<double> Ux = load_m3<double>(gptr<double>(U, g, p, mu), g.vs, active ? cb : 0);
     M = mscale(beta / 6.0, proj_ta(mmul(Ux, A)));
   }
   emit_block<LAYOUT>(g, out, p, blk, lane, mu, mode, dt, M, active, lex_of(g, c), sh, sh_site);
@@ -348,7 +348,7 @@ __device__ __forceinline__ double link_trsq(const Geom& g, const double2* __rest
   } else {
     const int cb = t % g.vh, pm = t / g.vh;  // pm = parity*4 + mu
 #pragma unroll
-    for (int k = 0; k < 9; ++k) m.m[k] = ld<double>(P + ((size_t)pm * 9 + k) * g.vh + cb);
+    for (int k = 0; k < 9; ++k) m.m[k] = ld<double>(P + ((size_t)pm * 9 + k) * g.vs + cb);
   }
   double tr = 0.0;
 #pragma unroll
@@ -396,8 +396,8 @@ __global__ __launch_bounds__(256) void k_link_update(Geom g, double2* __restrict
     stride = 1;
   } else {
     const int cb = t % g.vh, pm = t / g.vh;
-    base = (size_t)pm * 9 * g.vh + cb;
-    stride = g.vh;
+    base = (size_t)pm * 9 * g.vs + cb;
+    stride = g.vs;
   }
   M3<double> u, x;
 #pragma unroll

@@ -467,21 +467,21 @@ hipError_t launch_hop_axpy(const Geom& g, int p_out, HopIn<R, T> hin, T* out_eve
   e.self[0] = self_even;
   e.self[1] = self_odd;
   e.coef = R(coef);
-  e.vh = g.vh;
+  e.vh = g.vs;
   return launch<R, DAG>(g, p_out, hin, e, nullptr, s);
 }
 
 template <typename R, typename T, bool DAG>
 hipError_t launch_hop_schur_norm(const Geom& g, HopIn<R, T> hin, T* w, const T* x, double coef, SolverState* st,
                                  Reduce red, hipStream_t s) {
-  EpiSchurNorm<R, T> e{w, x, R(coef), g.vh, st};
+  EpiSchurNorm<R, T> e{w, x, R(coef), g.vs, st};
   return launch<R, DAG>(g, 1, hin, e, red.partials, s, red.capacity);
 }
 
 template <typename R, typename T, bool DAG>
 hipError_t launch_hop_schur_cg(const Geom& g, HopIn<R, T> hin, const T* w, R2<R>* x, R2<R>* r, const T* p,
                                double coef, SolverState* st, Reduce red, hipStream_t s) {
-  EpiSchurCG<R, T> e{w, x, r, p, R(coef), g.vh, st};
+  EpiSchurCG<R, T> e{w, x, r, p, R(coef), g.vs, st};
   return launch<R, DAG>(g, 1, hin, e, red.partials, s, red.capacity);
 }
 
@@ -489,7 +489,7 @@ template <bool DAG>
 hipError_t launch_hop_residual(const Geom& g, HopIn<double> hin, const double2* self_full,
                                const double2* phi_full, double2* r_full, double coef, Reduce red,
                                int slot, hipStream_t s) {
-  const size_t half = (size_t)12 * g.vh;
+  const size_t half = (size_t)12 * g.vs;
   EpiResidual e;
   e.self[0] = self_full;
   e.self[1] = self_full + half;
@@ -498,7 +498,7 @@ hipError_t launch_hop_residual(const Geom& g, HopIn<double> hin, const double2* 
   e.r[0] = r_full;
   e.r[1] = r_full + half;
   e.coef = coef;
-  e.vh = g.vh;
+  e.vh = g.vs;
   hipError_t err = launch<double, DAG>(g, -1, hin, e, red.partials, s, red.capacity);
   if (err != hipSuccess) return err;
   return launch_finalize(kFinResult1, 2 * nblk_parity(g), red, nullptr, slot, 0.0, 0, s);
@@ -511,7 +511,7 @@ hipError_t launch_hop_step(const Geom& g, const R2<R>* gauge, int nk, R2<R>* t, 
   e.t = t;
   e.p = p;
   e.r = r;
-  e.vh = g.vh;
+  e.vh = g.vs;
   e.state = st;
   e.partials = red.partials;
   e.nblk = nblk_parity(g);

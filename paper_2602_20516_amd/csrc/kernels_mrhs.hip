@@ -1,8 +1,9 @@
 // Multi-right-hand-side kernels: nr spinor fields on one lattice, solved
 // together (one pseudofermion per right-hand side, each with its own kappa).
 //
-// Layout of a multi-RHS half field: [12 components][nr][V/2 sites] complex
-// (site fastest), a full field the even half then the odd half.  Every
+// Layout of a multi-RHS half field: [12 components][nr][vs] complex (site
+// fastest, planes vs >= V/2 sites apart; their padding holds anything finite
+// or not and is never summed, since it moves with nr), a full field the even half then the odd half.  Every
 // per-component access of a wave is unit stride, as in the single field.
 //
 // Hop decomposition: a 256-thread block owns 64 consecutive sites of one
@@ -131,13 +132,13 @@ struct MEpiResidual {  // r = phi - (self + coef_n acc), per-RHS |r|^2 (both par
 
 
 // Loader of one right-hand side of a multi-RHS field: element (k, n, site)
-// at (k*nr + n)*vh + site; the per-lane offset carries site and n, the
+// at (k*nr + n)*vs + site; the per-lane offset carries site and n, the
 // component offset is uniform.
 template <typename R>
 struct MrhsIn {
   BufRsrc rs;
-  unsigned ks;  // component stride in bytes (nr * vh elements)
-  unsigned ns;  // right-hand-side stride in bytes (vh elements)
+  unsigned ks;  // component stride in bytes (nr * vs elements)
+  unsigned ns;  // right-hand-side stride in bytes (vs elements)
   __device__ __forceinline__ unsigned off(int site, int n) const {
     return (unsigned)site * (unsigned)sizeof(R2<R>) + (unsigned)n * ns;
   }
@@ -180,8 +181,8 @@ __global__ __launch_bounds__(256) void k_hop_mrhs(Geom g, int nr, int G, int nbp
   __syncthreads();
   const unsigned act = s_act;
   constexpr unsigned E = sizeof(R2<R>);
-  const unsigned gs = (unsigned)g.vh * E;
-  const unsigned ns = (unsigned)g.vh * E;
+  const unsigned gs = (unsigned)g.vs * E;
+  const unsigned ns = (unsigned)g.vs * E;
   const MrhsIn<R> in{make_rsrc(p ? hin.in_even : hin.in_odd, (size_t)12 * nr * ns), (unsigned)nr * ns, ns};
   int c[4] = {0, 0, 0, 0};
   int nf = 0, nb = 0;
@@ -194,8 +195,8 @@ __global__ __launch_bounds__(256) void k_hop_mrhs(Geom g, int nr, int G, int nbp
   // of SU(3) links with the third rebuilt in registers (a third less link
   // traffic per group, as in the single-field hop)
   const int nk = hin.nk;
-  const BufRsrc ruf = make_rsrc(hin.gauge + (size_t)((p * 4 + mu) * nk) * g.vh, (size_t)nk * gs);
-  const BufRsrc rub = make_rsrc(hin.gauge + (size_t)(((1 - p) * 4 + mu) * nk) * g.vh, (size_t)nk * gs);
+  const BufRsrc ruf = make_rsrc(hin.gauge + (size_t)((p * 4 + mu) * nk) * g.vs, (size_t)nk * gs);
+  const BufRsrc rub = make_rsrc(hin.gauge + (size_t)(((1 - p) * 4 + mu) * nk) * g.vs, (size_t)nk * gs);
   constexpr bool kKeepLinks = sizeof(R) == 4;
   M3<R> Uf, Ub;
 #pragma unroll
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(256) void k_hop_mrhs(Geom g, int nr, int G, int nbp
       for (int i = 0; i < 3; ++i) {
         const int k = 3 * mu + i;
         const R2<R> a = lds[0][k][lane], b = lds[1][k][lane], cc = lds[2][k][lane], d = lds[3][k][lane];
-        epi.apply(p, ((size_t)k * nr + n) * g.vh + cb, n,
+        epi.apply(p, ((size_t)k * nr + n) * g.vs + cb, n,
                   cmk<R>(((a.x + b.x) + cc.x) + d.x, ((a.y + b.y) + cc.y) + d.y), red);
       }
     }
@@ -411,7 +412,7 @@ __device__ __forceinline__ void mfma_dir(const Geom& g, const MrhsIn<float>& in,
                                          const int c[4], int j, int n0, unsigned live, C<float> (*out)[12]) {
   constexpr int SF = DAG ? +1 : -1;
   constexpr unsigned E = sizeof(float2);
-  const unsigned gs = (unsigned)g.vh * E;
+  const unsigned gs = (unsigned)g.vs * E;
   const int nf = cb_shift(g, c, MU, +1), nb = cb_shift(g, c, MU, -1);
   const BufRsrc ruf = make_rsrc(gptr<float>(gauge, g, p, MU), (size_t)9 * gs);
   const BufRsrc rub = make_rsrc(gptr<float>(gauge, g, 1 - p, MU), (size_t)9 * gs);
@@ -448,7 +449,7 @@ __global__ __launch_bounds__(256) void k_hop_mrhs_mfma(Geom g, int nr, int nbp, 
   __syncthreads();
   const unsigned act = s_act;
   constexpr unsigned E = sizeof(float2);
-  const unsigned ns = (unsigned)g.vh * E;
+  const unsigned ns = (unsigned)g.vs * E;
   const MrhsIn<float> in{make_rsrc(p ? hin.in_even : hin.in_odd, (size_t)12 * nr * ns), (unsigned)nr * ns, ns};
   C<float> out[NL][12];
 #pragma unroll
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(256) void k_hop_mrhs_mfma(Geom g, int nr, int nbp, 
     for (int k = kq; k < 12; k += KS) {
       const float2 a = lds[0][nl][k][site], b = lds[1][nl][k][site], cc = lds[2][nl][k][site],
                    d = lds[3][nl][k][site];
-      epi.apply(p, ((size_t)k * nr + n) * g.vh + ocb, n, cmk<float>(((a.x + b.x) + cc.x) + d.x,
+      epi.apply(p, ((size_t)k * nr + n) * g.vs + ocb, n, cmk<float>(((a.x + b.x) + cc.x) + d.x,
                                                                      ((a.y + b.y) + cc.y) + d.y), red);
     }
   }
@@ -578,7 +579,7 @@ template <bool DAG>
 hipError_t launch_mhop_residual(const Geom& g, int nr, int G, HopIn<double> hin, const double2* self_full,
                                 const double2* phi_full, double2* r_full, const double* coef, Reduce red,
                                 hipStream_t s) {
-  const size_t half = (size_t)12 * g.vh * nr;
+  const size_t half = (size_t)12 * g.vs * nr;
   MEpiResidual e;
   e.self[0] = self_full;
   e.self[1] = self_full + half;
@@ -611,23 +612,24 @@ template hipError_t launch_mhop_residual<true>(const Geom&, int, int, HopIn<doub
                                                const double2*, double2*, const double*, Reduce, hipStream_t);
 
 // ---------------------------------------------------------------------------
-// Vector kernels over multi-RHS fields: grid (site blocks, 12 * nr slabs);
+// Vector kernels over multi-RHS fields (padding included, except in sums):
+// grid (site blocks, 12 * nr slabs);
 // slab s of a half field holds component s / nr of right-hand side s % nr.
 // ---------------------------------------------------------------------------
-static inline dim3 slab_grid(int vh, int nr) { return dim3((vh + 255) / 256, 12 * nr); }
+static inline dim3 slab_grid(int vs, int nr) { return dim3((vs + 255) / 256, 12 * nr); }
 
 // per-RHS |a|^2 over ncomp components (12: half field, 24: full field):
 // grid (nbx, nr), block (bx, n) sums its sites over all components into
 // partials [bx][kMaxRhs]
 template <typename R>
-__global__ __launch_bounds__(256) void k_mnorm(int vh, int ncomp, int nr, const R2<R>* __restrict__ a,
+__global__ __launch_bounds__(256) void k_mnorm(int vh, int vs, int ncomp, int nr, const R2<R>* __restrict__ a,
                                                double* partials) {
   __shared__ double sh[4];
   const int n = blockIdx.y;
   double acc = 0.0;
   for (int s = blockIdx.x * 256 + threadIdx.x; s < vh; s += gridDim.x * 256) {
     for (int k = 0; k < ncomp; ++k) {
-      const R2<R> v = a[((size_t)k * nr + n) * vh + s];
+      const R2<R> v = a[((size_t)k * nr + n) * vs + s];
       acc += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
     }
   }
@@ -641,15 +643,15 @@ static inline int mnorm_blocks(int vh) {
 }
 
 template <typename R>
-hipError_t launch_mnorm(int vh, int ncomp, int nr, const R2<R>* a, Reduce red, hipStream_t s) {
+hipError_t launch_mnorm(int vh, int vs, int ncomp, int nr, const R2<R>* a, Reduce red, hipStream_t s) {
   const int nb = mnorm_blocks(vh);
-  hipLaunchKernelGGL((k_mnorm<R>), dim3(nb, nr), dim3(256), 0, s, vh, ncomp, nr, a, red.partials);
+  hipLaunchKernelGGL((k_mnorm<R>), dim3(nb, nr), dim3(256), 0, s, vh, vs, ncomp, nr, a, red.partials);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_mfinalize(kFinResult1, nb, nr, red, nullptr, 0.0, 0, s);
 }
-template hipError_t launch_mnorm<double>(int, int, int, const double2*, Reduce, hipStream_t);
-template hipError_t launch_mnorm<float>(int, int, int, const float2*, Reduce, hipStream_t);
+template hipError_t launch_mnorm<double>(int, int, int, int, const double2*, Reduce, hipStream_t);
+template hipError_t launch_mnorm<float>(int, int, int, int, const float2*, Reduce, hipStream_t);
 
 // After the finalize of an iteration: x += alpha_n p for every right-hand
 // side whose recursion ran it (still running, or stopped by this finalize:
@@ -658,7 +660,7 @@ template hipError_t launch_mnorm<float>(int, int, int, const float2*, Reduce, hi
 // p = r + beta_n p where the recursion goes on or waits for the update.  The x update is here rather than in the Schur-CG
 // epilogue because this kernel reads p anyway.
 template <typename R>
-__global__ __launch_bounds__(256) void k_mxpay(int vh, int nr, const R2<R>* __restrict__ r, R2<R>* __restrict__ p,
+__global__ __launch_bounds__(256) void k_mxpay(int vs, int nr, const R2<R>* __restrict__ r, R2<R>* __restrict__ p,
                                                R2<R>* __restrict__ x, const BatchState* st) {
   if (st->idle) return;  // a queued iteration after the batch stopped: nothing ran
   const int n = blockIdx.y % nr;
@@ -667,8 +669,8 @@ __global__ __launch_bounds__(256) void k_mxpay(int vh, int nr, const R2<R>* __re
   const bool upd = d == kDoneRunning || d == kDoneUpdate;
   if (!ran && !upd) return;
   const int s = blockIdx.x * 256 + threadIdx.x;
-  if (s >= vh) return;
-  const size_t i = (size_t)blockIdx.y * vh + s;
+  if (s >= vs) return;
+  const size_t i = (size_t)blockIdx.y * vs + s;
   R2<R> pv = p[i];
   if (ran) {
     const R alpha = R(st->alpha[n]);
@@ -686,19 +688,19 @@ __global__ __launch_bounds__(256) void k_mxpay(int vh, int nr, const R2<R>* __re
   }
 }
 template <typename R>
-hipError_t launch_mxpay(int vh, int nr, const R2<R>* r, R2<R>* p, R2<R>* x, BatchState* st, hipStream_t s) {
-  hipLaunchKernelGGL((k_mxpay<R>), slab_grid(vh, nr), dim3(256), 0, s, vh, nr, r, p, x, st);
+hipError_t launch_mxpay(int vs, int nr, const R2<R>* r, R2<R>* p, R2<R>* x, BatchState* st, hipStream_t s) {
+  hipLaunchKernelGGL((k_mxpay<R>), slab_grid(vs, nr), dim3(256), 0, s, vs, nr, r, p, x, st);
   return hipGetLastError();
 }
 template hipError_t launch_mxpay<double>(int, int, const double2*, double2*, double2*, BatchState*, hipStream_t);
 template hipError_t launch_mxpay<float>(int, int, const float2*, float2*, float2*, BatchState*, hipStream_t);
 
 // x64 += scale_n * xs; xs = 0
-__global__ __launch_bounds__(256) void k_mmixed_update(int vh, int nr, float2* xs, double2* __restrict__ x,
+__global__ __launch_bounds__(256) void k_mmixed_update(int vs, int nr, float2* xs, double2* __restrict__ x,
                                                        const double* __restrict__ scale) {
   const int s = blockIdx.x * 256 + threadIdx.x;
-  if (s >= vh) return;
-  const size_t i = (size_t)blockIdx.y * vh + s;
+  if (s >= vs) return;
+  const size_t i = (size_t)blockIdx.y * vs + s;
   const double sc = scale[blockIdx.y % nr];
   const float2 v = xs[i];
   double2 xv = x[i];
@@ -707,20 +709,20 @@ __global__ __launch_bounds__(256) void k_mmixed_update(int vh, int nr, float2* x
   x[i] = xv;
   xs[i] = make_float2(0.f, 0.f);
 }
-hipError_t launch_mmixed_update(int vh, int nr, float2* xs, double2* x, const double* scale, hipStream_t s) {
-  hipLaunchKernelGGL(k_mmixed_update, slab_grid(vh, nr), dim3(256), 0, s, vh, nr, xs, x, scale);
+hipError_t launch_mmixed_update(int vs, int nr, float2* xs, double2* x, const double* scale, hipStream_t s) {
+  hipLaunchKernelGGL(k_mmixed_update, slab_grid(vs, nr), dim3(256), 0, s, vs, nr, xs, x, scale);
   return hipGetLastError();
 }
 
 // r = sigma_n r64; p = r (restart_n) or p *= pscale_n
-__global__ __launch_bounds__(256) void k_mrescale(int vh, int nr, const double2* __restrict__ r64,
+__global__ __launch_bounds__(256) void k_mrescale(int vs, int nr, const double2* __restrict__ r64,
                                                   const double* __restrict__ sigma, float2* __restrict__ r,
                                                   float2* __restrict__ p, const int* __restrict__ restart,
                                                   const double* __restrict__ pscale) {
   const int s = blockIdx.x * 256 + threadIdx.x;
-  if (s >= vh) return;
+  if (s >= vs) return;
   const int n = blockIdx.y % nr;
-  const size_t i = (size_t)blockIdx.y * vh + s;
+  const size_t i = (size_t)blockIdx.y * vs + s;
   const double sg = sigma[n];
   const double2 v = r64[i];
   const float2 w = make_float2((float)(sg * v.x), (float)(sg * v.y));
@@ -732,9 +734,9 @@ __global__ __launch_bounds__(256) void k_mrescale(int vh, int nr, const double2*
     p[i] = make_float2((float)(pscale[n] * (double)q.x), (float)(pscale[n] * (double)q.y));
   }
 }
-hipError_t launch_mrescale(int vh, int nr, const double2* r64, const double* sigma, float2* r, float2* p,
+hipError_t launch_mrescale(int vs, int nr, const double2* r64, const double* sigma, float2* r, float2* p,
                            const int* restart, const double* pscale, hipStream_t s) {
-  hipLaunchKernelGGL(k_mrescale, slab_grid(vh, nr), dim3(256), 0, s, vh, nr, r64, sigma, r, p, restart, pscale);
+  hipLaunchKernelGGL(k_mrescale, slab_grid(vs, nr), dim3(256), 0, s, vs, nr, r64, sigma, r, p, restart, pscale);
   return hipGetLastError();
 }
 
@@ -748,14 +750,14 @@ __global__ __launch_bounds__(256) void k_mcg_init64(size_t n, const double2* __r
     x[i] = make_double2(0.0, 0.0);
   }
 }
-hipError_t launch_mcg_init64(int vh, int nr, const double2* b, double2* r, double2* p, double2* x, BatchState* st,
+hipError_t launch_mcg_init64(int vh, int vs, int nr, const double2* b, double2* r, double2* p, double2* x, BatchState* st,
                              Reduce red, double tol, int max_iter, hipStream_t s) {
-  const size_t n = (size_t)12 * vh * nr;
+  const size_t n = (size_t)12 * vs * nr;
   hipLaunchKernelGGL(k_mcg_init64, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, b, r, p, x);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int nb = mnorm_blocks(vh);
-  hipLaunchKernelGGL((k_mnorm<double>), dim3(nb, nr), dim3(256), 0, s, vh, 12, nr, b, red.partials);
+  hipLaunchKernelGGL((k_mnorm<double>), dim3(nb, nr), dim3(256), 0, s, vh, vs, 12, nr, b, red.partials);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_mfinalize(kFinCgInit, nb, nr, red, st, tol, max_iter, s);
@@ -884,18 +886,18 @@ hipError_t launch_mfinalize(int mode, int nblk, int nr, Reduce red, BatchState* 
   return hipGetLastError();
 }
 
-// element (k, n, site) of a multi-RHS field is at (k nr + n) vh + site
-__global__ __launch_bounds__(256) void k_mzero_rhs(size_t tot, int vh, int nr, double2* __restrict__ f,
+// element (k, n, site) of a multi-RHS field is at (k nr + n) vs + site
+__global__ __launch_bounds__(256) void k_mzero_rhs(size_t tot, int vs, int nr, double2* __restrict__ f,
                                                    unsigned mask) {
   const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (t >= tot) return;
-  const int n = (int)((t / (size_t)vh) % (size_t)nr);
+  const int n = (int)((t / (size_t)vs) % (size_t)nr);
   if ((mask >> n) & 1u) f[t] = make_double2(0.0, 0.0);
 }
-hipError_t launch_mzero_rhs(int vh, int ncomp, int nr, double2* f, unsigned mask, hipStream_t s) {
+hipError_t launch_mzero_rhs(int vs, int ncomp, int nr, double2* f, unsigned mask, hipStream_t s) {
   if (!mask) return hipSuccess;
-  const size_t tot = (size_t)ncomp * nr * vh;
-  hipLaunchKernelGGL(k_mzero_rhs, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, tot, vh, nr, f, mask);
+  const size_t tot = (size_t)ncomp * nr * vs;
+  hipLaunchKernelGGL(k_mzero_rhs, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, tot, vs, nr, f, mask);
   return hipGetLastError();
 }
 
@@ -907,7 +909,7 @@ __global__ __launch_bounds__(256) void k_mpack(Geom g, int nr, int n, const doub
   const int s = (int)(t / 12), k = (int)(t % 12);
   int c[4];
   lex_coords(g, s, c);
-  packed[(((size_t)parity_of(c) * 12 + k) * nr + n) * g.vh + (s >> 1)] = canon[t];
+  packed[(((size_t)parity_of(c) * 12 + k) * nr + n) * g.vs + (s >> 1)] = canon[t];
 }
 __global__ __launch_bounds__(256) void k_munpack(Geom g, int nr, int n, const double2* __restrict__ packed,
                                                  double2* __restrict__ canon) {
@@ -916,7 +918,7 @@ __global__ __launch_bounds__(256) void k_munpack(Geom g, int nr, int n, const do
   const int s = (int)(t / 12), k = (int)(t % 12);
   int c[4];
   lex_coords(g, s, c);
-  canon[t] = packed[(((size_t)parity_of(c) * 12 + k) * nr + n) * g.vh + (s >> 1)];
+  canon[t] = packed[(((size_t)parity_of(c) * 12 + k) * nr + n) * g.vs + (s >> 1)];
 }
 hipError_t launch_mpack(const Geom& g, int nr, int n, const double2* canon, double2* packed, hipStream_t s) {
   const size_t tot = 2 * (size_t)g.vh * 12;

@@ -157,10 +157,10 @@ __global__ __launch_bounds__(256) void k_stout_fwd(Geom g, const double2* __rest
                                                    double rho) {
   LinkIdx li;
   if (!link_of_thread(g, li)) return;
-  const M3<double> Ux = load_m3<double>(gptr<double>(U, g, li.p, li.mu), g.vh, li.cb);
+  const M3<double> Ux = load_m3<double>(gptr<double>(U, g, li.p, li.mu), g.vs, li.cb);
   const M3<double> A = staple_A(U, g, li.c, li.mu);
   const M3<double> X = mscale(-rho, proj_ta(mmul(Ux, A)));
-  store_m3<double>((double2*)gptr<double>(Uo, g, li.p, li.mu), g.vh, li.cb, mmul(exp_ah(X), Ux));
+  store_m3<double>((double2*)gptr<double>(Uo, g, li.p, li.mu), g.vs, li.cb, mmul(exp_ah(X), Ux));
 }
 
 __global__ __launch_bounds__(256) void k_stout_adj_a(Geom g, const double2* __restrict__ U,
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256) void k_stout_adj_a(Geom g, const double2* __re
                                                      double2* __restrict__ Lam, double2* __restrict__ Gpart) {
   LinkIdx li;
   if (!link_of_thread(g, li)) return;
-  const int vh = g.vh;
+  const int vh = g.vs;
   const M3<double> Ux = load_m3<double>(gptr<double>(U, g, li.p, li.mu), vh, li.cb);
   const M3<double> A = staple_A(U, g, li.c, li.mu);
   const M3<double> X = mscale(-rho, proj_ta(mmul(Ux, A)));
@@ -228,8 +228,8 @@ __global__ __launch_bounds__(256) void k_stout_adj_b(Geom g, const double2* __re
       S = mmac(S, mmul_dn(Um_ymm, Ua_ymm), link_at(Lam, g, ymmpa, m));
     }
   }
-  const M3<double> Gx = load_m3<double>(gptr<double>(Gpart, g, li.p, a), g.vh, li.cb);
-  store_m3<double>((double2*)gptr<double>(Go, g, li.p, a), g.vh, li.cb, madd(Gx, mscale(rho, S)));
+  const M3<double> Gx = load_m3<double>(gptr<double>(Gpart, g, li.p, a), g.vs, li.cb);
+  store_m3<double>((double2*)gptr<double>(Go, g, li.p, a), g.vs, li.cb, madd(Gx, mscale(rho, S)));
 }
 
 // out (packed or canonical) accumulates the force of a gradient G at U:
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256) void k_grad_to_force(Geom g, const double2* __
                                                        double2* __restrict__ out) {
   LinkIdx li;
   if (!link_of_thread(g, li)) return;
-  const int vh = g.vh;
+  const int vh = g.vs;
   const M3<double> Gx = load_m3<double>(gptr<double>(G, g, li.p, li.mu), vh, li.cb);
   M3<double> add;
   if (mode == 1) {

@@ -90,13 +90,14 @@ int lgt_ctx_max_shifts();
 struct lgt_ctx {
   lgt::Geom g{};
   int64_t V = 0;
-  int vh = 0;
+  int vh = 0;  // sites per parity
+  int vs = 0;  // plane stride of the packed fields (g.vs)
   hipStream_t stream = nullptr;
   int device = 0;
   std::string err;
 
-  // packed links: FP64 [2][4][9][vh], FP32 copy (mixed precision), and the
-  // first two rows [2][4][6][vh] of each for the CG hops
+  // packed links: FP64 [2][4][9][vs], FP32 copy (mixed precision), and the
+  // first two rows [2][4][6][vs] of each for the CG hops
   double2* U64 = nullptr;
   float2* U32 = nullptr;
   float2* U32c = nullptr;
@@ -104,10 +105,10 @@ struct lgt_ctx {
   // packed momenta for the MD driver
   double2* P64 = nullptr;
 
-  // spinor workspace: FP64 full fields (24*vh complex each) and FP32 half fields
+  // spinor workspace: FP64 full fields (24*vs complex each) and FP32 half fields
   std::vector<double2*> full64;
   std::vector<float2*> half32;
-  // packed FP64 gauge-type scratch fields (72*vh complex each)
+  // packed FP64 gauge-type scratch fields (72*vs complex each)
   std::vector<double2*> gauge64;
 
   // reductions / solver state
@@ -122,8 +123,8 @@ struct lgt_ctx {
   lgt::Mailbox* mbox_dev = nullptr;         // its device address
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
 
-  size_t half_elems() const { return (size_t)12 * vh; }
-  size_t full_elems() const { return (size_t)24 * vh; }
+  size_t half_elems() const { return (size_t)12 * vs; }
+  size_t full_elems() const { return (size_t)24 * vs; }
   lgt::Reduce red() const {
     return lgt::Reduce{partials, result, lgt::reduce_capacity(vh), (size_t)lgt::reduce_capacity(vh) * 4, mbox_dev};
   }

@@ -307,6 +307,7 @@ struct Geom {
   int L[4];   // Lx, Ly, Lz, Lt
   int hx;     // Lx / 2
   int vh;     // V / 2 (sites per parity)
+  int vs;     // stride between the component planes of a packed field, >= vh (plane_stride)
   int bc;     // fermion temporal boundary sign
   int hop_ns; // sites per hop block: 32 or 64, or 0 to choose by volume
   int hop_order;  // order of the 64-site blocks: 1 site order, 2 t-fastest groups, 0 by volume
@@ -346,9 +347,9 @@ __device__ __forceinline__ void shifted(const Geom& g, const int c[4], int mu, i
   n[mu] = v < 0 ? v + g.L[mu] : (v >= g.L[mu] ? v - g.L[mu] : v);
 }
 
-// Packed gauge-type field: [parity][mu][9][vh] complex, element (i,j) at k = 3i+j.
+// Packed gauge-type field: [parity][mu][9][vs] complex, element (i,j) at k = 3i+j.
 template <typename R> __device__ __forceinline__ const R2<R>* gptr(const R2<R>* f, const Geom& g, int p, int mu) {
-  return f + (size_t)((p * 4 + mu) * 9) * g.vh;
+  return f + (size_t)((p * 4 + mu) * 9) * g.vs;
 }
 template <typename R> __device__ __forceinline__ M3<R> load_m3(const R2<R>* f, int vh, int cb) {
   M3<R> u;

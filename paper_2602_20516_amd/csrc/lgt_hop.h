@@ -85,7 +85,7 @@ struct SpinorIn {
 // loader for the input parity of output parity p
 template <typename R, typename T>
 __device__ __forceinline__ SpinorIn<R, T> make_loader(const HopIn<R, T>& h, const Geom& g, int p, int nr) {
-  const unsigned ks = (unsigned)g.vh * (unsigned)nr * (unsigned)sizeof(T);
+  const unsigned ks = (unsigned)g.vs * (unsigned)nr * (unsigned)sizeof(T);
   return SpinorIn<R, T>{make_rsrc(p ? h.in_even : h.in_odd, (size_t)12 * ks), ks, (unsigned)nr};
 }
 
@@ -136,8 +136,8 @@ template <typename R>
 __device__ __forceinline__ M3<R> load_link(const R2<R>* __restrict__ gauge, int nk, const Geom& g, int p, int mu,
                                            int cb) {
   constexpr unsigned E = sizeof(R2<R>);
-  const unsigned gs = (unsigned)g.vh * E;
-  const BufRsrc ru = make_rsrc(gauge + (size_t)((p * 4 + mu) * nk) * g.vh, (size_t)nk * gs);
+  const unsigned gs = (unsigned)g.vs * E;
+  const BufRsrc ru = make_rsrc(gauge + (size_t)((p * 4 + mu) * nk) * g.vs, (size_t)nk * gs);
   // A link field larger than the last-level cache is read with the
   // non-temporal policy: each launch reads every link once, and kept in the
   // caches the links would only push out the spinors the neighbouring sites
@@ -232,9 +232,9 @@ __device__ __forceinline__ void hop_one(const Geom& g, const R2<R>* __restrict__
   for (int k = 0; k < 12; ++k) psi[k] = in.ld(o, k);
   project_s<R, MU>(psi, s, h);
   // U_mu(x) of parity p at cb, or U_mu(x - mu) of parity 1 - p at nb
-  const unsigned gs = (unsigned)g.vh * E;
+  const unsigned gs = (unsigned)g.vs * E;
   const BufRsrc ru = make_rsrc(gauge, (size_t)8 * nk * gs);
-  const unsigned lo = ((unsigned)(((bwd ? 1 - p : p) * 4 + MU) * nk) * (unsigned)g.vh + (unsigned)(bwd ? nb : cb)) * E;
+  const unsigned lo = ((unsigned)(((bwd ? 1 - p : p) * 4 + MU) * nk) * (unsigned)g.vs + (unsigned)(bwd ? nb : cb)) * E;
   M3<R> U;
   if (nk == 9) {
 #pragma unroll

@@ -113,6 +113,13 @@ constexpr int kHopHalfWaveMaxVh = 8192;
 // t-fastest (when a t-slice holds a whole number of blocks).
 constexpr int kHopTOrderMinVh = 131072;
 
+// Stride, in sites, between the component planes of a packed field with vh
+// sites per parity.  The padding of spinor planes holds zeros (buffers are
+// cleared when allocated and every vector kernel keeps zeros zero), so sums
+// over whole fields may run over it; the padding of link planes holds
+// nothing and is never read as a link.
+int plane_stride(int vh);
+
 // Reduction capacity needed for a lattice with vh sites per parity: the
 // largest reducing grid is the both-parity hop (2 * ceil(vh/32) blocks at
 // most).

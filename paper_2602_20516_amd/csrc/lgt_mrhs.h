@@ -28,7 +28,7 @@ hipError_t launch_mfinalize(int mode, int nblk, int nr, Reduce red, BatchState* 
 // rows of per-RHS partials a reducing batched hop writes (one per site block)
 int mrhs_hop_blocks(const Geom& g, int p_out);
 
-// Batched hops over nr fields in the [12][nr][vh] layout; G = right-hand
+// Batched hops over nr fields in the [12][nr][vs] layout; G = right-hand
 // sides per block (1..nr; the links are loaded once per group of G) for the
 // VALU kernel, or G = -4 / -8 for the MFMA kernel (FP32 only) with groups
 // of 4 or 8 right-hand sides.
@@ -54,17 +54,17 @@ hipError_t launch_mhop_residual(const Geom& g, int nr, int G, HopIn<double> hin,
 
 // result[n] = |a_n|^2 over a multi-RHS field of ncomp components (12 half, 24 full)
 template <typename R>
-hipError_t launch_mnorm(int vh, int ncomp, int nr, const R2<R>* a, Reduce red, hipStream_t s);
+hipError_t launch_mnorm(int vh, int vs, int ncomp, int nr, const R2<R>* a, Reduce red, hipStream_t s);
 // half-field updates, per right-hand side n
 template <typename R>
-hipError_t launch_mxpay(int vh, int nr, const R2<R>* r, R2<R>* p, R2<R>* x, BatchState* st, hipStream_t s);
-hipError_t launch_mmixed_update(int vh, int nr, float2* xs, double2* x, const double* scale, hipStream_t s);
-hipError_t launch_mrescale(int vh, int nr, const double2* r64, const double* sigma, float2* r, float2* p,
+hipError_t launch_mxpay(int vs, int nr, const R2<R>* r, R2<R>* p, R2<R>* x, BatchState* st, hipStream_t s);
+hipError_t launch_mmixed_update(int vs, int nr, float2* xs, double2* x, const double* scale, hipStream_t s);
+hipError_t launch_mrescale(int vs, int nr, const double2* r64, const double* sigma, float2* r, float2* p,
                            const int* restart, const double* pscale, hipStream_t s);
-hipError_t launch_mcg_init64(int vh, int nr, const double2* b, double2* r, double2* p, double2* x,
+hipError_t launch_mcg_init64(int vh, int vs, int nr, const double2* b, double2* r, double2* p, double2* x,
                              BatchState* st, Reduce red, double tol, int max_iter, hipStream_t s);
 // zero right-hand side n of a multi-RHS FP64 field of ncomp components for every bit n of mask
-hipError_t launch_mzero_rhs(int vh, int ncomp, int nr, double2* f, unsigned mask, hipStream_t s);
+hipError_t launch_mzero_rhs(int vs, int ncomp, int nr, double2* f, unsigned mask, hipStream_t s);
 hipError_t launch_mpack(const Geom& g, int nr, int n, const double2* canon, double2* packed, hipStream_t s);
 hipError_t launch_munpack(const Geom& g, int nr, int n, const double2* packed, double2* canon, hipStream_t s);
 

@@ -52,7 +52,7 @@ __device__ __forceinline__ int gauge_site_block(int lb, const BlockOrder& o, int
 }
 
 __device__ __forceinline__ M3<double> link_at(const double2* U, const Geom& g, const int c[4], int mu) {
-  return load_m3<double>(gptr<double>(U, g, parity_of(c), mu), g.vh, cb_of(g, c));
+  return load_m3<double>(gptr<double>(U, g, parity_of(c), mu), g.vs, cb_of(g, c));
 }
 
 

@@ -274,6 +274,7 @@ SolveStats lgt_ctx::solve_multishift(const double2* phi, int ns, const double* s
   double2* q = w->q;
   for (int i = 0; i < ns; ++i) {
     double2* xi = w->X + (size_t)i * h;
+    if (vs != vh) LGT_HIP(launch_zero64(n, q, stream));  // the padding, whatever an earlier call left there
     apply_mhat_dag_mhat64(false, xi, q);
     LGT_HIP(launch_axpy64(n, shifts[i], xi, q, stream));
     LGT_HIP(launch_xmy64(n, phio, q, stream));  // q = phi_o - (A + sigma_i) X_i
@@ -306,7 +307,7 @@ SolveStats lgt_ctx::rational_force(const double2* phi, int ns, const double* shi
   MultiShiftWork* w = mshift;
   const size_t h = half_elems();
   const int n = (int)h;
-  const int ng = 72 * vh;  // complex elements of a gauge-type field
+  const int ng = 72 * vs;  // complex elements of a gauge-type field
   const double2* phio = phi + h;
   double2* xf = f64(kStageA);  // (H_eo X_o, X_o)
   double2* af = f64(kE);       // (H_oe^dag Y_o, Y_o)
@@ -341,7 +342,7 @@ SolveStats lgt_ctx::rational_force(const double2* phi, int ns, const double* shi
   }
   if (S) *S = sr;
   // the output: overwritten (force, gradient) or updated in place (momentum)
-  if (mode != LGT_OUT_MOMENTUM) LGT_HIP(launch_zero64(ng, (double2*)out, stream));
+  if (mode != LGT_OUT_MOMENTUM) LGT_HIP(launch_zero64(72 * vh, (double2*)out, stream));
   const int acc = mode == LGT_OUT_FORCE ? 0 : (mode == LGT_OUT_GRAD ? 1 : 2);
   LGT_HIP(launch_grad_to_force(g, U64, gsum, acc, dt, out, kCanonical, stream));
   return st;

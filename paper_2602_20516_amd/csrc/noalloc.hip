@@ -75,6 +75,7 @@ lgt_status lgt_dslash_noalloc(const lgt_geom* geom, void* hip_stream, const void
     for (int i = 0; i < 4; ++i) g.L[i] = geom->dims[i];
     g.hx = geom->dims[0] / 2;
     g.vh = (int)(V / 2);
+    g.vs = g.vh;  // the scratch has no room for padded planes
     g.bc = geom->fermion_t_bc;
     g.hop_ns = 0;
     g.hop_order = 0;

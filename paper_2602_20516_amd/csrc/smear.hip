@@ -20,13 +20,13 @@ enum { kPing = 0, kPong = 1, kLam = 2, kGpart = 3, kGtmp = 4, kGf = 5, kRecomp =
 
 double2* lgt_ctx::g64(int i) {
   if ((int)gauge64.size() <= i) gauge64.resize(i + 1, nullptr);
-  if (!gauge64[i]) LGT_HIP(hipMalloc(&gauge64[i], (size_t)72 * vh * sizeof(double2)));
+  if (!gauge64[i]) LGT_HIP(hipMalloc(&gauge64[i], (size_t)72 * vs * sizeof(double2)));
   return gauge64[i];
 }
 
 // dst must not be one of the intermediate buffers 0/1.
 void lgt_ctx::smear(const double2* U0, int n, double rho, double2* dst) {
-  const int ncx = 72 * vh;
+  const int ncx = 72 * vs;
   if (n == 0) {
     LGT_HIP(launch_copy64(ncx, U0, dst, stream));
     return;
@@ -49,7 +49,7 @@ int lgt_ctx::stout_slots(int n) {
   if (want <= have) return want;
   size_t fr = 0, tot = 0;
   LGT_HIP(hipMemGetInfo(&fr, &tot));
-  const size_t slot = (size_t)72 * vh * sizeof(double2);
+  const size_t slot = (size_t)72 * vs * sizeof(double2);
   const size_t reserve = tot / 8;
   const int64_t extra = fr > reserve ? (int64_t)((fr - reserve) / slot) : 0;
   return (int)std::min<int64_t>(want, have + extra);
@@ -66,7 +66,7 @@ const StoutSchedule& lgt_ctx::stout_plan(int n) {
 // checkpoints in slots 0, 1, ...; dst must not be a smearing intermediate.
 void lgt_ctx::smear_checkpointed(const double2* U0, int n, double rho, double2* dst, const StoutSchedule& plan) {
   if (n == 0) {
-    LGT_HIP(launch_copy64(72 * vh, U0, dst, stream));
+    LGT_HIP(launch_copy64(72 * vs, U0, dst, stream));
     return;
   }
   const std::vector<int> cp = plan.forward_checkpoints();
@@ -149,7 +149,7 @@ void lgt_ctx::stout_backprop(const double2* U0, int n, double rho, double2* G, c
   }
   if (rv.passes != plan.cost())
     throw Error(LGT_ERR_DEVICE, "internal error: stout reverse pass departed from its schedule");
-  if (rv.gin != G) LGT_HIP(launch_copy64(72 * vh, rv.gin, G, stream));
+  if (rv.gin != G) LGT_HIP(launch_copy64(72 * vs, rv.gin, G, stream));
   last_stout_slots = s;
   last_stout_passes = rv.passes;
 }
@@ -161,7 +161,7 @@ SolveStats lgt_ctx::smeared_force(const double2* U0, const double2* phi, double 
   smear_checkpointed(U0, n, rho, U64, plan);
   if (o.precision != LGT_FP64) {
     ensure_u32();
-    LGT_HIP(launch_convert_64_32(72 * vh, U64, U32, stream));
+    LGT_HIP(launch_convert_64_32(72 * vs, U64, U32, stream));
   }
   SolveStats st = solve_ddagd(phi, f64(kX), f64(kY), o);
   if (S_F) *S_F = action_fermion(phi, f64(kX), f64(kY));

@@ -49,25 +49,25 @@ float2* lgt_ctx::h32(int i) {
 }
 
 void lgt_ctx::ensure_u32() {
-  if (!U32) LGT_HIP(hipMalloc(&U32, (size_t)72 * vh * sizeof(float2)));
+  if (!U32) LGT_HIP(hipMalloc(&U32, (size_t)72 * vs * sizeof(float2)));
 }
 
 void lgt_ctx::compress_links() {
-  if (!U32c) LGT_HIP(hipMalloc(&U32c, (size_t)48 * vh * sizeof(float2)));
+  if (!U32c) LGT_HIP(hipMalloc(&U32c, (size_t)48 * vs * sizeof(float2)));
   LGT_HIP(hipMemsetAsync(flags + 1, 0, sizeof(int), stream));
   LGT_HIP(launch_compress_links(g, U32, U32c, flags + 1, stream));
   LGT_HIP(hipMemcpyAsync(host_flags + 1, flags + 1, sizeof(int), hipMemcpyDeviceToHost, stream));
 }
 
 void lgt_ctx::compress_links64() {
-  if (!U64c) LGT_HIP(hipMalloc(&U64c, (size_t)48 * vh * sizeof(double2)));
+  if (!U64c) LGT_HIP(hipMalloc(&U64c, (size_t)48 * vs * sizeof(double2)));
   LGT_HIP(hipMemsetAsync(flags + 2, 0, sizeof(int), stream));
   LGT_HIP(launch_compress_links(g, U64, U64c, flags + 2, stream));
   LGT_HIP(hipMemcpyAsync(host_flags + 2, flags + 2, sizeof(int), hipMemcpyDeviceToHost, stream));
 }
 
 void lgt_ctx::ensure_p64() {
-  if (!P64) LGT_HIP(hipMalloc(&P64, (size_t)72 * vh * sizeof(double2)));
+  if (!P64) LGT_HIP(hipMalloc(&P64, (size_t)72 * vs * sizeof(double2)));
 }
 
 void lgt_ctx::sync() { LGT_HIP(hipStreamSynchronize(stream)); }
