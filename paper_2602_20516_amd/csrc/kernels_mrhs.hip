@@ -231,12 +231,8 @@ __global__ __launch_bounds__(256) void k_hop_mrhs(Geom g, int nr, int G, int nbp
         Uf.m[k] = ld_buf<R>(ruf, (unsigned)cb * E, k * gs);
         Ub.m[k] = ld_buf<R>(rub, (unsigned)nb * E, k * gs);
       }
-      Uf.m[6] = conj(Uf.m[1] * Uf.m[5] - Uf.m[2] * Uf.m[4]);
-      Uf.m[7] = conj(Uf.m[2] * Uf.m[3] - Uf.m[0] * Uf.m[5]);
-      Uf.m[8] = conj(Uf.m[0] * Uf.m[4] - Uf.m[1] * Uf.m[3]);
-      Ub.m[6] = conj(Ub.m[1] * Ub.m[5] - Ub.m[2] * Ub.m[4]);
-      Ub.m[7] = conj(Ub.m[2] * Ub.m[3] - Ub.m[0] * Ub.m[5]);
-      Ub.m[8] = conj(Ub.m[0] * Ub.m[4] - Ub.m[1] * Ub.m[3]);
+      third_row(Uf);
+      third_row(Ub);
     }
   }
   for (int n = n0; n < n1; ++n) {
