@@ -181,12 +181,12 @@ LGT_API lgt_status lgt_dslash(lgt_ctx* ctx, const void* U, const void* in, void*
  * the same operator, kernels and results, with no context and no allocation.
  * geom: the lattice (as lgt_create); hip_stream: the stream the work is
  * enqueued on (NULL = default stream); U, in, out, kappa, dagger as
- * lgt_dslash (device pointers, canonical layouts).  Working storage (packed
- * links and spinors, 960 bytes per site) is a device array built into the
- * library, one copy per GPU, held until the process ends; it limits the
- * lattice to V <= 65536 sites (16^4).  Every call on one GPU uses that GPU's
- * copy: calls that overlap in time on one GPU (different streams or threads)
- * race, calls ordered on one stream do not.  Returns once the work is
+ * lgt_dslash (device pointers, canonical layouts).  One launch that reads and
+ * writes the caller's fields.  Where out lies over an input, working storage
+ * (packed links and spinors, 960 bytes per site) is a device array built into
+ * the library, one copy per GPU, held until the process ends; it limits every
+ * call to V <= 65536 sites (16^4).  Calls of that kind that overlap in time on
+ * one GPU (different streams or threads) race.  Returns once the work is
  * enqueued; no NaN/Inf check of the inputs (non-finite values reach out).
  * Errors: INVALID_ARGUMENT (null pointer, odd or < 2 extent, bc not +-1,
  * non-finite kappa, V > 65536), DEVICE; message via lgt_last_error(NULL). */
@@ -476,7 +476,7 @@ LGT_API lgt_status lgt_hop_benchmark_mrhs(lgt_ctx* ctx, const void* U, const voi
                                           int32_t precision, int32_t nrep, double* avg_ms);
 
 /* Work shape of the single-field hop kernel (the Wilson hop of eq. S3.1 in
- * every solve, force and dslash call of the context): sites = 64 gives each
+ * every solve and force call of the context): sites = 64 gives each
  * 256-thread block 64 sites, each wave both hops along one direction;
  * sites = 32 gives a block 32 sites, each half-wave one of the two hops, so
  * a small lattice runs twice as many waves.  0 (the default) takes 32 up to

@@ -243,6 +243,13 @@ lgt_status lgt_dslash(lgt_ctx* c, const void* U, const void* in, void* out, doub
   return guarded(c, [&] {
     require(U && in && out, "null field pointer");
     require(std::isfinite(kappa), "kappa must be finite");
+    const size_t spinor = (size_t)12 * c->V * sizeof(double2);
+    if (!overlap(in, spinor, out, spinor) && !overlap(U, 3 * spinor, out, spinor)) {
+      LGT_HIP(launch_dslash_direct(c->g, (const double2*)U, (const double2*)in, (double2*)out, kappa, dagger != 0,
+                                   c->stream));
+      return;
+    }
+    // an output over an input: through packed copies
     pack_links(c, U, false);
     double2* a = c->f64(kStageA);
     double2* b = c->f64(kStageB);

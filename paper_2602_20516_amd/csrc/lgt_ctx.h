@@ -32,6 +32,12 @@ struct Error : std::runtime_error {
                          std::string(#call) + ": " + hipGetErrorString(e_));                \
   } while (0)
 
+// whether the na bytes at a and the nb bytes at b share any
+inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + nb && y < x + na;
+}
+
 struct SolveStats {
   int iters = 0;
   int reliable = 0;

@@ -185,6 +185,11 @@ hipError_t launch_hop_residual(const Geom& g, HopIn<double> hin, const double2* 
                                const double2* phi_full, double2* r_full, double coef, Reduce red,
                                int slot, hipStream_t s);
 
+// out = psi - kappa H psi (or H^dag) on the caller's canonical fields, in one
+// launch (kernels_dslash.hip); out must not overlap U or psi
+hipError_t launch_dslash_direct(const Geom& g, const double2* U, const double2* psi, double2* out, double kappa,
+                                bool dag, hipStream_t s);
+
 // Vector kernels (kernels_field.hip).  n = number of complex elements.
 // End of a CG iteration: rr = sum of the nblk |r|^2 partials of (4), beta =
 // rr / rr_prev, the stop test (target, reliable-update threshold, iteration

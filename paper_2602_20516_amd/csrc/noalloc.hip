@@ -3,14 +3,15 @@
 // allocate (code under HIP graph capture, serving loops, harnesses that
 // forbid hipMalloc).
 //
-// Its working storage -- the packed links and the packed input and output
-// spinors lgt_dslash keeps in its context -- lives in one file-scope device
-// array, `scratch`, sized for lattices of up to kNoAllocMaxSites sites.  Each
-// GPU the library runs on holds its own copy of the array until the process
-// ends.  Host code never passes the array's name to a kernel (on the host it
+// It is the one launch of launch_dslash_direct, which reads and writes the
+// caller's fields only.  A call whose output lies over one of its inputs
+// instead goes through packed copies, as lgt_dslash does; their storage lives
+// in one file-scope device array, `scratch`, sized for lattices of up to
+// kNoAllocMaxSites sites.  Each GPU the library runs on holds its own copy of
+// the array until the process ends.  Host code never passes the array's name to a kernel (on the host it
 // is a stand-in symbol, not a device address): the first call on a device
 // looks up that device's address with hipGetSymbolAddress, and every launch
-// takes that pointer.  All calls on one GPU share the array, so calls that
+// takes that pointer.  All such calls on one GPU share the array, so ones that
 // overlap in time on one GPU (different streams or threads) race; calls
 // ordered on one stream do not.  The packing kernels write every element the
 // hop then reads, so nothing has to start at zero.
@@ -75,11 +76,16 @@ lgt_status lgt_dslash_noalloc(const lgt_geom* geom, void* hip_stream, const void
     for (int i = 0; i < 4; ++i) g.L[i] = geom->dims[i];
     g.hx = geom->dims[0] / 2;
     g.vh = (int)(V / 2);
-    g.vs = g.vh;  // the scratch has no room for padded planes
+    g.vs = g.vh;
     g.bc = geom->fermion_t_bc;
     g.hop_ns = 0;
     g.hop_order = 0;
     const hipStream_t s = (hipStream_t)hip_stream;
+    const size_t spinor = (size_t)12 * V * sizeof(double2);
+    if (!overlap(in, spinor, out, spinor) && !overlap(U, 3 * spinor, out, spinor)) {
+      LGT_HIP(launch_dslash_direct(g, (const double2*)U, (const double2*)in, (double2*)out, kappa, dagger != 0, s));
+      return LGT_OK;
+    }
     double2* base = scratch_on_current_device();
     double2* links = base;                      // 72 vh
     double2* a = links + (size_t)72 * g.vh;     // 24 vh: packed input (even half, then odd)
