@@ -222,6 +222,92 @@ hipError_t launch_bilinear_force(const Geom& g, const double2* U, const double2*
   return hipGetLastError();
 }
 
+// The sum over the terms of a rational force (see BilinearSum): the block of
+// k_bilinear_sb with a loop over the terms inside, whose own-site spinors
+// carry the weights into LDS.  The link sum Z stays in registers for a whole
+// group of terms, so the links, the projection and the output are paid once
+// for all terms; written out per term (a packed gradient, its sum, a pass that
+// projects it) each cost three gauge fields of traffic more.
+__global__ __launch_bounds__(256) void k_bilinear_sum(Geom g, const double2* __restrict__ U, BilinearSum t,
+                                                      double2* __restrict__ zsum, bool first, bool last,
+                                                      double kappa, double coeff, int mode, double dt, double2* out,
+                                                      BlockOrder order) {
+  __shared__ double2 smem[kSB * 36];  // [2][12][64] own-site spinors; the output staging
+  __shared__ int sh_site[kSB];
+  double2 (*sa)[kSB] = reinterpret_cast<double2 (*)[kSB]>(smem);
+  double2 (*sb)[kSB] = reinterpret_cast<double2 (*)[kSB]>(smem + 12 * kSB);
+  double2 (*sh)[36] = reinterpret_cast<double2 (*)[36]>(smem);
+  const int lb = xcd_block(blockIdx.x, gridDim.x);
+  const int p = lb & 1, blk = gauge_site_block(lb, order, g.L[2]);
+  const int lane = threadIdx.x & 63, mu = threadIdx.x >> 6;
+  const int cb = blk * kSB + lane;
+  const bool active = cb < g.vh;
+  const int cbx = active ? cb : 0;
+  int c[4];
+  cb_coords(g, p, cbx, c);
+  const int nf = cb_shift(g, c, mu, +1);
+  const unsigned ks = (unsigned)g.vs * (unsigned)sizeof(double2);
+  double2* zl = zsum + (size_t)((p * 4 + mu) * 9) * g.vs + cbx;
+  M3<double> Z;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) Z.m[k] = first ? czero<double>() : ld<double>(zl + (size_t)k * g.vs);
+  for (int i = 0; i < t.n; ++i) {
+    const double2* a[2] = {t.ae + i * t.stride, t.ao + i * t.stride};
+    const double2* b[2] = {t.be + i * t.stride, t.bo + i * t.bo_stride};
+    const double2 *ap = p ? a[1] : a[0], *bp = p ? b[1] : b[0], *an = p ? a[0] : a[1], *bn = p ? b[0] : b[1];
+    const double wt = t.weight[i];
+    if (i > 0) __syncthreads();  // every wave is done with the last term's spinors
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      const int e = threadIdx.x + 256 * j;
+      const int f = e / (12 * kSB), k = (e % (12 * kSB)) / kSB, l = e % kSB;
+      const int site = blk * kSB + l;
+      double2 v = make_double2(0.0, 0.0);
+      if (site < g.vh) v = (f ? bp : ap)[(size_t)k * g.vs + site];
+      (f ? sb : sa)[k][l] = make_double2(wt * v.x, wt * v.y);
+    }
+    const SpinorIn<double, double2> a_nb{make_rsrc(an, (size_t)12 * ks), ks, 1u};
+    const SpinorIn<double, double2> b_nb{make_rsrc(bn, (size_t)12 * ks), ks, 1u};
+    __syncthreads();
+    M3<double> z;
+    switch (mu) {
+      case 0: z = bilinear_z<0>(sa, sb, a_nb, b_nb, lane, nf); break;
+      case 1: z = bilinear_z<1>(sa, sb, a_nb, b_nb, lane, nf); break;
+      case 2: z = bilinear_z<2>(sa, sb, a_nb, b_nb, lane, nf); break;
+      default: z = bilinear_z<3>(sa, sb, a_nb, b_nb, lane, nf); break;
+    }
+    Z = madd(Z, z);
+  }
+  if (!last) {
+    if (active) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) st<double>(zl + (size_t)k * g.vs, Z.m[k]);
+    }
+    return;
+  }
+  const double sbc = (mu == 3 && c[3] == g.L[3] - 1) ? double(g.bc) : 1.0;
+  M3<double> M;
+  if (mode == 1) {
+    M = mscale(-coeff * kappa * sbc, mdag(Z));
+  } else {
+    const M3<double> Ux = load_m3<double>(gptr<double>(U, g, p, mu), g.vs, cbx);
+    M = mscale(0.5 * coeff * kappa * sbc, proj_ta(mmul(Ux, Z)));
+  }
+  __syncthreads();  // every wave is done with sa, sb before sh overwrites them
+  emit_block<kCanonical>(g, out, p, blk, lane, mu, mode, dt, M, active, lex_of(g, c), sh, sh_site);
+}
+
+hipError_t launch_bilinear_sum(const Geom& g, const double2* U, const BilinearSum& t, double2* zsum, bool first,
+                               bool last, double kappa, double coeff, int mode, double dt, void* out,
+                               hipStream_t s) {
+  if (t.n < 0 || t.n > kBilinearTerms) return hipErrorInvalidValue;
+  BlockOrder order = gauge_block_order(g);
+  order.nyc = 0;
+  hipLaunchKernelGGL(k_bilinear_sum, dim3(sb_blocks(g)), dim3(256), 0, s, g, U, t, zsum, first, last, kappa, coeff,
+                     mode, dt, (double2*)out, order);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // Wilson plaquette action: the link U_mu(x) enters S_G through
 // -(beta/3) Re tr(U_mu(x) A_mu(x)) with the staple sum

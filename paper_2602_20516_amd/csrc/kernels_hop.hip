@@ -173,6 +173,78 @@ struct EpiStep {
   __device__ void tail() const {}
 };
 
+// First hop of a multi-shift iteration: t = H (r + beta p) = H r + beta t and
+// p = r + beta p as in EpiStep, with beta and the stop decision from the
+// state, where the finalize that advances the shifts has left them.
+struct EpiDirection {
+  static constexpr bool kReduce = false;
+  static constexpr bool kPrefetch = true;
+  double2* t;
+  double2* p;
+  const double2* r;
+  int vh;
+  const SolverState* state;
+  __device__ bool skip() const { return state->done != kDoneRunning; }
+  struct Pre {
+    C<double> t[3], r[3], p[3];
+  };
+  __device__ Pre pre(int, int cb, int spin) const {
+    Pre q;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const size_t o = (size_t)(3 * spin + i) * vh + cb;
+      q.t[i] = ld<double>(t + o);
+      q.r[i] = ld<double>(r + o);
+      q.p[i] = ld<double>(p + o);
+    }
+    return q;
+  }
+  __device__ void apply(int, int cb, int spin, const C<double>* acc, double&, const Pre& q) const {
+    const double b = state->beta;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const size_t o = (size_t)(3 * spin + i) * vh + cb;
+      lgt::st<double>(t + o, acc[i] + b * q.t[i]);
+      lgt::st<double>(p + o, q.r[i] + b * q.p[i]);
+    }
+  }
+  template <int NT>
+  __device__ void tail() const {}
+};
+
+// Last hop of a shifted true residual: block partials of
+// |phi - (w + coef * acc) - sigma x|^2 (odd sites); nothing is stored.
+struct EpiShiftResidual {
+  static constexpr bool kReduce = true;
+  static constexpr bool kPrefetch = true;
+  const double2* w;
+  const double2* x;
+  const double2* phi;
+  double sigma, coef;
+  int vh;
+  __device__ bool skip() const { return false; }
+  struct Pre {
+    C<double> w[3], x[3], f[3];
+  };
+  __device__ Pre pre(int, int cb, int spin) const {
+    Pre q;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const size_t o = (size_t)(3 * spin + i) * vh + cb;
+      q.w[i] = ld<double>(w + o);
+      q.x[i] = ld<double>(x + o);
+      q.f[i] = ld<double>(phi + o);
+    }
+    return q;
+  }
+  __device__ void apply(int, int, int, const C<double>* acc, double& red, const Pre& q) const {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) red += norm2(q.f[i] - ((q.w[i] + coef * acc[i]) + sigma * q.x[i]));
+  }
+  template <int NT>
+  __device__ void tail() const {}
+};
+
 template <typename R, typename T>
 struct EpiSchurNorm {  // w = x + coef * acc (odd sites), block partials of |w|^2 (of w as stored)
   static constexpr bool kReduce = true;
@@ -206,12 +278,13 @@ struct EpiSchurNorm {  // w = x + coef * acc (odd sites), block partials of |w|^
 };
 
 template <typename R, typename T>
-struct EpiSchurCG {  // q = w + coef * acc; x += alpha p (if x); r -= alpha q; block partials of |r|^2
+struct EpiSchurCG {  // q = w + coef * acc; x += alpha p (if x); ro = r - alpha q; block partials of |ro|^2
   static constexpr bool kReduce = true;
   static constexpr bool kPrefetch = !std::is_same<T, Bf16c>::value;
   const T* w;
   R2<R>* x;
-  R2<R>* r;
+  const R2<R>* r;
+  R2<R>* ro;  // may be r
   const T* p;
   R coef;
   int vh;
@@ -242,7 +315,7 @@ struct EpiSchurCG {  // q = w + coef * acc; x += alpha p (if x); r -= alpha q; b
       const C<R> q = pq.w[i] + coef * acc[i];
       if (x) st<R>(x + o, pq.x[i] + alpha * pq.p[i]);
       C<R> rv = pq.r[i] - alpha * q;
-      st<R>(r + o, rv);
+      st<R>(ro + o, rv);
       red += (double)rv.re * (double)rv.re + (double)rv.im * (double)rv.im;
     }
   }
@@ -479,9 +552,9 @@ hipError_t launch_hop_schur_norm(const Geom& g, HopIn<R, T> hin, T* w, const T* 
 }
 
 template <typename R, typename T, bool DAG>
-hipError_t launch_hop_schur_cg(const Geom& g, HopIn<R, T> hin, const T* w, R2<R>* x, R2<R>* r, const T* p,
-                               double coef, SolverState* st, Reduce red, hipStream_t s) {
-  EpiSchurCG<R, T> e{w, x, r, p, R(coef), g.vs, st};
+hipError_t launch_hop_schur_cg(const Geom& g, HopIn<R, T> hin, const T* w, R2<R>* x, const R2<R>* r, R2<R>* ro,
+                               const T* p, double coef, SolverState* st, Reduce red, hipStream_t s) {
+  EpiSchurCG<R, T> e{w, x, r, ro, p, R(coef), g.vs, st};
   return launch<R, DAG>(g, 1, hin, e, red.partials, s, red.capacity);
 }
 
@@ -520,6 +593,16 @@ hipError_t launch_hop_step(const Geom& g, const R2<R>* gauge, int nk, R2<R>* t, 
   const HopIn<R> hin{gauge, r, r, nk};
   return launch<R, DAG>(g, 0, hin, e, nullptr, s);
 }
+hipError_t launch_hop_direction(const Geom& g, const double2* gauge, int nk, double2* t, double2* p,
+                                const double2* r, const SolverState* st, hipStream_t s) {
+  return launch<double, false>(g, 0, HopIn<double>{gauge, r, r, nk}, EpiDirection{t, p, r, g.vs, st}, nullptr, s);
+}
+hipError_t launch_hop_shift_residual(const Geom& g, HopIn<double> hin, const double2* w, const double2* x,
+                                     const double2* phi, double sigma, double coef, double* partials,
+                                     hipStream_t s) {
+  return launch<double, true>(g, 1, hin, EpiShiftResidual{w, x, phi, sigma, coef, g.vs}, partials, s,
+                              hop_blocks(g, 1));
+}
 template hipError_t launch_hop_step<double, false>(const Geom&, const double2*, int, double2*, double2*,
                                                    const double2*, SolverState*, Reduce, hipStream_t);
 template hipError_t launch_hop_step<double, true>(const Geom&, const double2*, int, double2*, double2*,
@@ -535,8 +618,9 @@ template hipError_t launch_hop_step<float, true>(const Geom&, const float2*, int
 #define LGT_INST_CG(R, T, DAG)                                                                            \
   template hipError_t launch_hop_schur_norm<R, T, DAG>(const Geom&, HopIn<R, T>, T*, const T*, double,       \
                                                         SolverState*, Reduce, hipStream_t);                 \
-  template hipError_t launch_hop_schur_cg<R, T, DAG>(const Geom&, HopIn<R, T>, const T*, R2<R>*, R2<R>*,     \
-                                                      const T*, double, SolverState*, Reduce, hipStream_t);
+  template hipError_t launch_hop_schur_cg<R, T, DAG>(const Geom&, HopIn<R, T>, const T*, R2<R>*,             \
+                                                      const R2<R>*, R2<R>*, const T*, double, SolverState*, Reduce, \
+                                                      hipStream_t);
 
 LGT_INST_AXPY(double, false, double2)
 LGT_INST_AXPY(double, true, double2)

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <chrono>
+#include <functional>
 #include <memory>
 #include <cstdint>
 #include <stdexcept>
@@ -228,8 +229,10 @@ struct lgt_ctx {
 
   // multi-shift CG (multishift.hip): X_i = (Mhat^dag Mhat + shifts[i])^-1 phi_o
   MultiShiftWork* mshift = nullptr;
+  using MultiShiftTerms =
+      std::function<void(int i0, int c, const double2* xe, const double2* yo, const double2* ae)>;
   lgt::SolveStats solve_multishift(const double2* phi, int ns, const double* shifts, void* const* Xout,
-                                   const lgt::SolverOpts& o);
+                                   const lgt::SolverOpts& o, const MultiShiftTerms& force = nullptr);
   // rational even/odd action and force (multishift.hip); out: canonical gauge field
   lgt::SolveStats rational_force(const double2* phi, int ns, const double* shifts, const double* residues, double a0,
                                  const lgt::SolverOpts& o, int mode, double dt, void* out, double* S);

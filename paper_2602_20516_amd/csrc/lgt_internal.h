@@ -173,11 +173,20 @@ hipError_t launch_hop_step(const Geom& g, const R2<R>* gauge, int nk, R2<R>* t, 
 template <typename R, typename T, bool DAG>
 hipError_t launch_hop_schur_norm(const Geom& g, HopIn<R, T> hin, T* w, const T* x, double coef, SolverState* st,
                                  Reduce red, hipStream_t s);
-// (x may be null: the multi-shift solver tracks no base solution).  The
-// |r|^2 partials are left for the caller's step or finalize kernel.
+// (x may be null: the multi-shift solver tracks no base solution).  ro = r -
+// alpha q; ro may be r.  The |ro|^2 partials are left for the caller's step
+// or finalize kernel.
 template <typename R, typename T, bool DAG>
-hipError_t launch_hop_schur_cg(const Geom& g, HopIn<R, T> hin, const T* w, R2<R>* x, R2<R>* r, const T* p,
-                               double coef, SolverState* st, Reduce red, hipStream_t s);
+hipError_t launch_hop_schur_cg(const Geom& g, HopIn<R, T> hin, const T* w, R2<R>* x, const R2<R>* r, R2<R>* ro,
+                               const T* p, double coef, SolverState* st, Reduce red, hipStream_t s);
+// t = H r + beta t, p = r + beta p with beta from the state (multi-shift CG);
+// a no-op once the solve has stopped
+hipError_t launch_hop_direction(const Geom& g, const double2* gauge, int nk, double2* t, double2* p,
+                                const double2* r, const SolverState* st, hipStream_t s);
+// block partials (hop_blocks(g, 1) of them) of |phi - (w + coef H^dag in) - sigma x|^2, odd sites
+hipError_t launch_hop_shift_residual(const Geom& g, HopIn<double> hin, const double2* w, const double2* x,
+                                     const double2* phi, double sigma, double coef, double* partials,
+                                     hipStream_t s);
 // Residual of the full operator: r = phi - (self + coef * H in) over both parities,
 // result[slot] = |r|^2
 template <bool DAG>
@@ -249,6 +258,21 @@ hipError_t launch_rescale_residual(int n, const double2* r64, double sigma, floa
 hipError_t launch_bilinear_force(const Geom& g, const double2* U, const double2* a_full,
                                  const double2* b_full, double kappa, double coeff, int mode, double dt,
                                  void* out, int layout, hipStream_t s);
+// The same for a weighted sum of bilinears, sum_i weight_i Re[a_i^dag D b_i],
+// in groups of up to kBilinearTerms terms: each launch reads the links' sum so
+// far from zsum (unless first) and either writes it back or (last) emits the
+// force or gradient in the canonical layout.  Half fields: a_i = (ae, ao) + i
+// stride, b_i = (be + i stride, bo + i bo_stride).
+constexpr int kBilinearTerms = 8;
+struct BilinearSum {
+  const double2 *ae, *ao, *be, *bo;
+  size_t stride, bo_stride;
+  int n;
+  double weight[kBilinearTerms];
+};
+hipError_t launch_bilinear_sum(const Geom& g, const double2* U, const BilinearSum& t, double2* zsum, bool first,
+                               bool last, double kappa, double coeff, int mode, double dt, void* out,
+                               hipStream_t s);
 hipError_t launch_gauge_force(const Geom& g, const double2* U, double beta, int mode, double dt,
                               void* out, int layout, hipStream_t s);
 // result[slot] = sum_x sum_{mu<nu} Re tr P_mu,nu(x); with Uold, the sum of

@@ -144,7 +144,7 @@ static void cg_iteration(const Geom& g, const R2<R>* gauge, double kappa, T* t, 
                                          red.partials)));
   // x += alpha p: in the fourth hop's epilogue on the fused path, else in the
   // step kernel, which reads p anyway
-  LGT_HIP((launch_hop_schur_cg<R, T, !DAG>(g, HopIn<R, T>{gauge, t2, t2, nk}, w, fuse ? x : nullptr, r, p, k2, st,
+  LGT_HIP((launch_hop_schur_cg<R, T, !DAG>(g, HopIn<R, T>{gauge, t2, t2, nk}, w, fuse ? x : nullptr, r, r, p, k2, st,
                                            red, s)));
   if (!fuse) LGT_HIP((launch_cg_step<R, T>(n, r, p, st, red, hop_blocks(g, 1), s, x)));
 }
