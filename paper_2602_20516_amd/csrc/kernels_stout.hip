@@ -13,6 +13,9 @@
 //   Omega = C U^dag  ->  Lambda := G_C = G_Omega U,  G_U += G_Omega^dag C
 //   C = rho sum of staples -> every link of every staple receives its share
 //   (stage B gathers the 18 terms per link).
+// Between the stages travels Q = G_Omega, which is traceless anti-Hermitian:
+// eight reals a link instead of the eighteen of Lambda = Q U, which stage B
+// needs only where it reads U as well.
 // Nothing is stored between levels: the caller recomputes U_{l-1} from U_0.
 #include "lgt_internal.h"
 #include "lgt_su3.h"
@@ -147,7 +150,7 @@ __device__ __forceinline__ bool link_of_thread(const Geom& g, LinkIdx& li) {
   const int lb = xcd_block(blockIdx.x, gridDim.x);
   li.p = lb & 1;
   li.cb = gauge_site_block(lb, gauge_block_order(g), g.L[2]) * 64 + (threadIdx.x & 63);
-  li.mu = threadIdx.x >> 6;
+  li.mu = wave_id();
   if (li.cb >= g.vh) return false;
   cb_coords(g, li.p, li.cb, li.c);
   return true;
@@ -165,7 +168,7 @@ __global__ __launch_bounds__(256) void k_stout_fwd(Geom g, const double2* __rest
 
 __global__ __launch_bounds__(256) void k_stout_adj_a(Geom g, const double2* __restrict__ U,
                                                      const double2* __restrict__ Gp, double rho,
-                                                     double2* __restrict__ Lam, double2* __restrict__ Gpart) {
+                                                     double2* __restrict__ Q, double2* __restrict__ Gpart) {
   LinkIdx li;
   if (!link_of_thread(g, li)) return;
   const int vh = g.vs;
@@ -178,7 +181,7 @@ __global__ __launch_bounds__(256) void k_stout_adj_a(Geom g, const double2* __re
   exp_adjoint_ah(X, GE, Einv, GX);  // E^dag, and L(X^dag, G_E) up to its non-su(3) part
   const M3<double> GOm = proj_ta(GX);
   const M3<double> C = mscale(rho, mdag(A));
-  store_m3<double>((double2*)gptr<double>(Lam, g, li.p, li.mu), vh, li.cb, mmul(GOm, Ux));
+  store_alg(Q, g, li.p, li.mu, li.cb, GOm);
   store_m3<double>((double2*)gptr<double>(Gpart, g, li.p, li.mu), vh, li.cb,
                    mmac_dn(mmul(Einv, G1), GOm, C));
 }
@@ -188,48 +191,56 @@ __global__ __launch_bounds__(256) void k_stout_adj_a(Geom g, const double2* __re
 // C_mu(x)/rho = sum_nu [U_nu(x) U_mu(x+nu) U_nu(x+mu)^dag
 //                       + U_nu(x-nu)^dag U_mu(x-nu) U_nu(x-nu+mu)], the link is
 // a side link of the staples of C_m (m != a) in four ways and the middle
-// link of the staples of C_a in two ways (per m != a):
+// link of the staples of C_a in two ways (per m != a), with L = Lambda:
 //   L_m(y) U_a(y+m) U_m(y+a)^dag      L_m(y-m)^dag U_a(y-m) U_m(y-m+a)
 //   U_m(y) U_a(y+m) L_m(y+a)^dag      U_m(y-m)^dag U_a(y-m) L_m(y-m+a)
 //   U_m(y-m)^dag L_a(y-m) U_m(y-m+a)  U_m(y) L_a(y+m) U_m(y+a)^dag
+// With L = Q U (Q^dag = -Q; nothing else is used of U), the three terms of the
+// forward side (U_1 = U_m(y), U_2 = U_a(y+m), U_3 = U_m(y+a)) and those of the
+// backward side (V_1 = U_m(y-m), V_2 = U_a(y-m), V_3 = U_m(y-m+a)) are
+//   Q_1 (U_1 A) + U_1 (Q_2 A - A Q_3),  A = U_2 U_3^dag
+//   V_1^dag [(R_2 - R_1) V_2 + V_2 R_3] V_3,
+// the ten products per m that the terms take with a stored Lambda.  The
+// kernel is bound by what it gathers past the L2 (24^3x48: 64 % of its reads
+// missed there, 10 GB in 1330 us with Lambda and U at every staple neighbour,
+// 1152 bytes a site); Q and U are 832.  One level's adjoint at 24^3x48 2.39 ->
+// 1.78 ms, at 32^3x64 6.9 -> 5.3 ms, of which stage A's smaller output is a
+// tenth.
 __global__ __launch_bounds__(256) void k_stout_adj_b(Geom g, const double2* __restrict__ U,
-                                                     const double2* __restrict__ Lam,
+                                                     const double2* __restrict__ Q,
                                                      const double2* __restrict__ Gpart, double rho,
                                                      double2* __restrict__ Go) {
   LinkIdx li;
   if (!link_of_thread(g, li)) return;
-  const int a = li.mu;
+  const int a = li.mu, p = li.p;
   const int* y = li.c;
-  M3<double> S;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) S.m[k] = czero<double>();
+  M3<double> S = mzero();
 #pragma unroll 1
   for (int k = 1; k < 4; ++k) {
     const int m = (a + k) & 3;
-    int ypm[4], ypa[4], ymm[4], ymmpa[4];
-    shifted(g, y, m, +1, ypm);
-    shifted(g, y, a, +1, ypa);
+    int ymm[4];
     shifted(g, y, m, -1, ymm);
-    shifted(g, ymm, a, +1, ymmpa);
-    // the first and third terms of each side share their last factor:
-    // five 3x3 products per side instead of six
+    const int ypm = cb_shift(g, y, m, +1), ypa = cb_shift(g, y, a, +1), cmm = cb_of(g, ymm),
+              ymmpa = cb_shift(g, ymm, a, +1);
     {  // forward side: sites y, y+m, y+a
-      const M3<double> Ua_ypm = link_at(U, g, ypm, a);
-      const M3<double> Um_y = link_at(U, g, y, m);
-      const M3<double> W = mmac(mmul(link_at(Lam, g, y, m), Ua_ypm), Um_y, link_at(Lam, g, ypm, a));
-      S = mmac_nd(S, W, link_at(U, g, ypa, m));
-      S = mmac_nd(S, mmul(Um_y, Ua_ypm), link_at(Lam, g, ypa, m));
+      const M3<double> A = mmul_nd(link_uni(U, g, 1 - p, a, ypm), link_uni(U, g, 1 - p, m, ypa));
+      const M3<double> U1 = link_uni(U, g, p, m, li.cb);
+      S = qmac(S, alg_uni(Q, g, p, m, li.cb), mmul(U1, A));
+      S = mmac(S, U1, macq(qmac(mzero(), alg_uni(Q, g, 1 - p, a, ypm), A), A, -alg_uni(Q, g, 1 - p, m, ypa)));
     }
+    // the backward side's loads stay behind the forward side's: hoisted above
+    // them they cost 3 % (held to 256 registers, two waves per SIMD, with a few
+    // spills: another 5 %)
+    asm volatile("" ::: "memory");
     {  // backward side: sites y-m, y-m+a
-      const M3<double> Ua_ymm = link_at(U, g, ymm, a);
-      const M3<double> Um_ymm = link_at(U, g, ymm, m);
-      const M3<double> W = mmac_dn(mmul_dn(link_at(Lam, g, ymm, m), Ua_ymm), Um_ymm, link_at(Lam, g, ymm, a));
-      S = mmac(S, W, link_at(U, g, ymmpa, m));
-      S = mmac(S, mmul_dn(Um_ymm, Ua_ymm), link_at(Lam, g, ymmpa, m));
+      const M3<double> V2 = link_uni(U, g, 1 - p, a, cmm);
+      const M3<double> W = macq(qmac(mzero(), alg_uni(Q, g, 1 - p, a, cmm) - alg_uni(Q, g, 1 - p, m, cmm), V2), V2,
+                                alg_uni(Q, g, p, m, ymmpa));
+      S = mmac(S, mmul_dn(link_uni(U, g, 1 - p, m, cmm), W), link_uni(U, g, p, m, ymmpa));
     }
   }
-  const M3<double> Gx = load_m3<double>(gptr<double>(Gpart, g, li.p, a), g.vs, li.cb);
-  store_m3<double>((double2*)gptr<double>(Go, g, li.p, a), g.vs, li.cb, madd(Gx, mscale(rho, S)));
+  const M3<double> Gx = load_m3<double>(gptr<double>(Gpart, g, p, a), g.vs, li.cb);
+  store_m3<double>((double2*)gptr<double>(Go, g, p, a), g.vs, li.cb, madd(Gx, mscale(rho, S)));
 }
 
 // out (packed or canonical) accumulates the force of a gradient G at U:
@@ -265,12 +276,12 @@ hipError_t launch_stout_fwd(const Geom& g, const double2* U, double2* Uo, double
   return hipGetLastError();
 }
 
-hipError_t launch_stout_adjoint(const Geom& g, const double2* U, const double2* Gp, double rho, double2* Lam,
+hipError_t launch_stout_adjoint(const Geom& g, const double2* U, const double2* Gp, double rho, double2* Q,
                                 double2* Gpart, double2* Go, hipStream_t s) {
-  hipLaunchKernelGGL(k_stout_adj_a, dim3(nb_links(g)), dim3(256), 0, s, g, U, Gp, rho, Lam, Gpart);
+  hipLaunchKernelGGL(k_stout_adj_a, dim3(nb_links(g)), dim3(256), 0, s, g, U, Gp, rho, Q, Gpart);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_stout_adj_b, dim3(nb_links(g)), dim3(256), 0, s, g, U, Lam, Gpart, rho, Go);
+  hipLaunchKernelGGL(k_stout_adj_b, dim3(nb_links(g)), dim3(256), 0, s, g, U, Q, Gpart, rho, Go);
   return hipGetLastError();
 }
 

@@ -289,8 +289,9 @@ hipError_t launch_link_update(const Geom& g, double2* U, const double2* P, doubl
 
 // Stout smearing (kernels_stout.hip), packed FP64 gauge fields.
 hipError_t launch_stout_fwd(const Geom& g, const double2* U, double2* Uo, double rho, hipStream_t s);
-// Adjoint of one level at input links U: Go = gradient at U given Gp at the output.
-hipError_t launch_stout_adjoint(const Geom& g, const double2* U, const double2* Gp, double rho, double2* Lam,
+// Adjoint of one level at input links U: Go = gradient at U given Gp at the
+// output.  Scratch: Q (32 vs complex), Gpart (72 vs).
+hipError_t launch_stout_adjoint(const Geom& g, const double2* U, const double2* Gp, double rho, double2* Q,
                                 double2* Gpart, double2* Go, hipStream_t s);
 // mode 0: out += F, 1: out += G, 2: out -= dt F, with F = -1/2 P[U G^dag]
 hipError_t launch_grad_to_force(const Geom& g, const double2* U, const double2* G, int mode, double dt, void* out,

@@ -56,6 +56,82 @@ __device__ __forceinline__ M3<double> link_at(const double2* U, const Geom& g, c
 }
 
 
+// The link U_mu of parity p at checkerboard site cb.  p and mu must be the
+// same for the whole wave: the load then takes one 32-bit offset a lane and
+// the component planes' offsets from scalar registers, no address arithmetic.
+__device__ __forceinline__ M3<double> link_uni(const double2* U, const Geom& g, int p, int mu, int cb) {
+  const unsigned gs = (unsigned)g.vs * (unsigned)sizeof(double2);
+  const BufRsrc r = make_rsrc(U + (size_t)((p * 4 + mu) * 9) * g.vs, (size_t)9 * gs);
+  M3<double> u;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) u.m[k] = ld_buf<double>(r, (unsigned)cb * (unsigned)sizeof(double2), k * gs);
+  return u;
+}
+
+// A traceless anti-Hermitian matrix Q as its eight real numbers: the upper
+// off-diagonal elements and the imaginary parts of the first two diagonal
+// ones.  Stored as four complex planes, [parity][mu][4][vs].
+struct Su3Alg {
+  C<double> o01, o02, o12;
+  double d0, d1;
+};
+__device__ __forceinline__ Su3Alg operator-(const Su3Alg& a, const Su3Alg& b) {
+  return {a.o01 - b.o01, a.o02 - b.o02, a.o12 - b.o12, a.d0 - b.d0, a.d1 - b.d1};
+}
+__device__ __forceinline__ Su3Alg operator-(const Su3Alg& a) { return {-a.o01, -a.o02, -a.o12, -a.d0, -a.d1}; }
+__device__ __forceinline__ void store_alg(double2* f, const Geom& g, int p, int mu, int cb, const M3<double>& q) {
+  double2* t = f + (size_t)((p * 4 + mu) * 4) * g.vs + cb;
+  st<double>(t, q.m[1]);
+  st<double>(t + g.vs, q.m[2]);
+  st<double>(t + 2 * (size_t)g.vs, q.m[5]);
+  st<double>(t + 3 * (size_t)g.vs, cmk<double>(q.m[0].im, q.m[4].im));
+}
+// p and mu uniform over the wave, as link_uni
+__device__ __forceinline__ Su3Alg alg_uni(const double2* f, const Geom& g, int p, int mu, int cb) {
+  const unsigned gs = (unsigned)g.vs * (unsigned)sizeof(double2), o = (unsigned)cb * (unsigned)sizeof(double2);
+  const BufRsrc r = make_rsrc(f + (size_t)((p * 4 + mu) * 4) * g.vs, (size_t)4 * gs);
+  const C<double> d = ld_buf<double>(r, o, 3 * gs);
+  return {ld_buf<double>(r, o, 0), ld_buf<double>(r, o, gs), ld_buf<double>(r, o, 2 * gs), d.re, d.im};
+}
+// s + i d b
+__device__ __forceinline__ C<double> cimac(C<double> s, double d, C<double> b) {
+  return {rfma(-d, b.im, s.re), rfma(d, b.re, s.im)};
+}
+// acc + Q b and acc + b Q
+__device__ __forceinline__ M3<double> qmac(const M3<double>& acc, const Su3Alg& q, const M3<double>& b) {
+  const C<double> l01 = -conj(q.o01), l02 = -conj(q.o02), l12 = -conj(q.o12);
+  M3<double> c;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const C<double> b0 = b.m[k], b1 = b.m[3 + k], b2 = b.m[6 + k];
+    c.m[k] = cmac(cmac(cimac(acc.m[k], q.d0, b0), q.o01, b1), q.o02, b2);
+    c.m[3 + k] = cmac(cimac(cmac(acc.m[3 + k], l01, b0), q.d1, b1), q.o12, b2);
+    c.m[6 + k] = cimac(cmac(cmac(acc.m[6 + k], l02, b0), l12, b1), -(q.d0 + q.d1), b2);
+  }
+  return c;
+}
+__device__ __forceinline__ M3<double> macq(const M3<double>& acc, const M3<double>& b, const Su3Alg& q) {
+  const C<double> l01 = -conj(q.o01), l02 = -conj(q.o02), l12 = -conj(q.o12);
+  M3<double> c;
+#pragma unroll
+  for (int i = 0; i < 9; i += 3) {
+    const C<double> b0 = b.m[i], b1 = b.m[i + 1], b2 = b.m[i + 2];
+    c.m[i] = cmac(cmac(cimac(acc.m[i], q.d0, b0), b1, l01), b2, l02);
+    c.m[i + 1] = cmac(cimac(cmac(acc.m[i + 1], b0, q.o01), q.d1, b1), b2, l12);
+    c.m[i + 2] = cimac(cmac(cmac(acc.m[i + 2], b0, q.o02), b1, q.o12), -(q.d0 + q.d1), b2);
+  }
+  return c;
+}
+__device__ __forceinline__ M3<double> mzero() {
+  M3<double> c;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) c.m[k] = czero<double>();
+  return c;
+}
+
+// wave index in the block as a scalar
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
 // Plaquette staple sum of the link U_mu(x):
 //   A = sum_{nu != mu} [ U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
 //                      + U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu) ],

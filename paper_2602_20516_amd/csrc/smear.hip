@@ -12,10 +12,10 @@
 using namespace lgt;
 
 namespace {
-// gauge scratch: 0/1 smearing intermediates, 2 Lambda, 3 partial gradient,
+// gauge scratch: 0/1 smearing intermediates, 2 su(3) cotangent, 3 partial gradient,
 // 4 gradient ping-pong, 5 fermion gradient, 6 thin links (ABI), 7 recomputed
 // level, 8 smeared output (ABI), 9-11 ABI; checkpoint slots from 16
-enum { kPing = 0, kPong = 1, kLam = 2, kGpart = 3, kGtmp = 4, kGf = 5, kRecomp = 7, kSlot0 = 16 };
+enum { kPing = 0, kPong = 1, kQ = 2, kGpart = 3, kGtmp = 4, kGf = 5, kRecomp = 7, kSlot0 = 16 };
 }  // namespace
 
 double2* lgt_ctx::g64(int i) {
@@ -97,7 +97,7 @@ struct Reverse {
     passes += m;
   }
   void adjoint(const double2* below) {  // gradient from U_l to U_{l-1}; below = U_{l-1}
-    LGT_HIP(launch_stout_adjoint(c->g, below, gin, rho, c->g64(kLam), c->g64(kGpart), gout, c->stream));
+    LGT_HIP(launch_stout_adjoint(c->g, below, gin, rho, c->g64(kQ), c->g64(kGpart), gout, c->stream));
     std::swap(gin, gout);
   }
   // segment [a, b]: U_a in ua, `free` slots from slot index `top` on
