@@ -964,7 +964,7 @@ lgt_status lgt_hop_benchmark(lgt_ctx* c, const void* U, const void* psi, int32_t
     if (f32) {
       a32 = c->h32(5);
       b32 = c->h32(6);
-      LGT_HIP(launch_convert_64_32((int)h, a + h, a32, c->stream));
+      LGT_HIP(launch_half_64_32(c->vs, 1, a + h, a32, c->stream));
     }
     // the links in the form the CG hops read them (two rows when they are SU(3))
     int nk = 9;

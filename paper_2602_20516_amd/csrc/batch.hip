@@ -222,8 +222,7 @@ struct BatchSolver {
     mhop<R, !DAG>(0, gauge, wv, t, nullptr, vec(vOne), w->st, w->partials, nullptr, nk);
     HopIn<R> h4{gauge, t, t, nk};
     // x += alpha p moves to the direction update, which reads p anyway
-    LGT_HIP((launch_mhop_schur_cg<R, !DAG>(c->g, nr, gsize<R>(), h4, wv, nullptr, r, p, vec(vMK2), w->st, red(),
-                                            c->stream)));
+    LGT_HIP((launch_mhop_schur_cg<R, !DAG>(c->g, nr, gsize<R>(), h4, wv, r, vec(vMK2), w->st, red(), c->stream)));
     LGT_HIP(launch_mxpay<R>(c->vs, nr, r, p, x, w->st, c->stream));
   }
 
@@ -500,8 +499,8 @@ void lgt_ctx::dslash_batch(int nr, const double* kappas, const void* const* ins,
   const Reduce red{w->partials, result, 0, w->npart, nullptr};
   if (f32) {
     // the half fields h[0], h[1] hold the even and odd FP32 input, h[2], h[3] the output
-    LGT_HIP(launch_convert_64_32((int)h, w->f[bPhi], w->h[0], stream));
-    LGT_HIP(launch_convert_64_32((int)h, w->f[bPhi] + h, w->h[1], stream));
+    LGT_HIP(launch_half_64_32(vs, nr, w->f[bPhi], w->h[0], stream));
+    LGT_HIP(launch_half_64_32(vs, nr, w->f[bPhi] + h, w->h[1], stream));
     HopIn<float> hin{U32, w->h[0], w->h[1]};
     if (dag)
       LGT_HIP((launch_mhop_axpy<float, true>(g, nr, G, -1, hin, w->h[2], w->h[3], w->h[0], w->h[1], mkap, stream,
@@ -538,7 +537,7 @@ double lgt_ctx::bench_mhop(int nr, bool f32, const void* psi, int nrep) {
   const float2* links32 = U32;
   int nk32 = 9;
   if (f32) {
-    LGT_HIP(launch_convert_64_32((int)h, w->f[bPhi] + h, w->h[0], stream));
+    LGT_HIP(launch_half_64_32(vs, nr, w->f[bPhi] + h, w->h[0], stream));
     compress_links();
     sync();
     if (host_flags[1] == 0 && G > 0) {

@@ -236,8 +236,45 @@ hipError_t launch_finalize(int mode, int nblk, Reduce red, SolverState* st, int 
   return hipGetLastError();
 }
 
+// Elements of the direction update: as many components as one 16-byte vector
+// of T holds, with the same components of the R2<R> fields x and r (two
+// vectors of them for BF16-stored p, whose planes hold a colour's four spins;
+// see Planes).  e: element, n / W of them; vs: plane stride.
+template <typename R, typename T> struct StepElem;
+template <> struct StepElem<double, double2> {
+  static constexpr int W = 1;
+  static __device__ __forceinline__ void ld_p(const double2* p, int e, C<double>* v) { v[0] = lgt::ld<double>(p + e); }
+  static __device__ __forceinline__ void st_p(double2* p, int e, const C<double>* v) { lgt::st<double>(p + e, v[0]); }
+  static __device__ __forceinline__ void ld_x(const double2* x, int e, int, C<double>* v) { v[0] = lgt::ld<double>(x + e); }
+  static __device__ __forceinline__ void st_x(double2* x, int e, int, const C<double>* v) { lgt::st<double>(x + e, v[0]); }
+};
+template <> struct StepElem<float, float2> {
+  static constexpr int W = 2;
+  static __device__ __forceinline__ void ld_p(const float2* p, int e, C<float>* v) {
+    halves(reinterpret_cast<const v4f32*>(p)[e], v[0], v[1]);
+  }
+  static __device__ __forceinline__ void st_p(float2* p, int e, const C<float>* v) {
+    reinterpret_cast<v4f32*>(p)[e] = v4f32{v[0].re, v[0].im, v[1].re, v[1].im};
+  }
+  static __device__ __forceinline__ void ld_x(const float2* x, int e, int, C<float>* v) { ld_p(x, e, v); }
+  static __device__ __forceinline__ void st_x(float2* x, int e, int, const C<float>* v) { st_p(x, e, v); }
+};
+template <> struct StepElem<float, Bf16c> {
+  static constexpr int W = 4;
+  static __device__ __forceinline__ void ld_p(const Bf16c* p, int e, C<float>* v) { Planes<float, Bf16c>::ld(p, 0, 0, e, v); }
+  static __device__ __forceinline__ void st_p(Bf16c* p, int e, const C<float>* v) { Planes<float, Bf16c>::st(p, 0, 0, e, v); }
+  static __device__ __forceinline__ void ld_x(const float2* x, int e, int vs, C<float>* v) {
+    const int own = e / vs;
+    Planes<float, float2>::ld(x, vs, own, e - own * vs, v);
+  }
+  static __device__ __forceinline__ void st_x(float2* x, int e, int vs, const C<float>* v) {
+    const int own = e / vs;
+    Planes<float, float2>::st(x, vs, own, e - own * vs, v);
+  }
+};
+
 template <typename R, typename T>
-__global__ __launch_bounds__(256) void k_cg_step(int n, int nblk, const double* __restrict__ partials,
+__global__ __launch_bounds__(256) void k_cg_step(int n, int vs, int nblk, const double* __restrict__ partials,
                                                  const R2<R>* __restrict__ r, T* __restrict__ p, SolverState* st,
                                                  Mailbox* mb, R2<R>* __restrict__ x) {
   const int done0 = st->done;
@@ -268,32 +305,32 @@ __global__ __launch_bounds__(256) void k_cg_step(int n, int nblk, const double* 
   else if (iter >= st->max_iter) code = kDoneMaxIter;
   {
     // x += alpha p (this iteration's step, taken whatever the decision), then
-    // p = r + beta p unless the recursion stops; four elements per thread and
+    // p = r + beta p unless the recursion stops; kTrip elements per thread and
     // trip, all loads issued before the stores
+    using E = StepElem<R, T>;
+    constexpr int kTrip = E::W == 4 ? 2 : 4;
     const R b = R(beta), a = R(st->alpha);
     const bool upd = code == kDoneRunning;
-    const int stride = gridDim.x * 256;
-    int i = blockIdx.x * 256 + threadIdx.x;
-    for (; i + 3 * stride < n; i += 4 * stride) {
-      C<R> rv[4], pv[4], xv[4];
+    const int stride = gridDim.x * 256, ne = n / E::W;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < ne; i += kTrip * stride) {
+      C<R> rv[kTrip][E::W], pv[kTrip][E::W], xv[kTrip][E::W];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        pv[j] = Store<R, T>::ld(p + i + j * stride);
-        xv[j] = ld<R>(x + i + j * stride);
-        if (upd) rv[j] = ld<R>(r + i + j * stride);
+      for (int j = 0; j < kTrip; ++j) {
+        if (i + j * stride >= ne) continue;
+        E::ld_p(p, i + j * stride, pv[j]);
+        E::ld_x(x, i + j * stride, vs, xv[j]);
+        if (upd) E::ld_x(r, i + j * stride, vs, rv[j]);
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        lgt::st<R>(x + i + j * stride, xv[j] + a * pv[j]);
-        if (upd) Store<R, T>::st(p + i + j * stride, C<R>{rv[j].re + b * pv[j].re, rv[j].im + b * pv[j].im});
-      }
-    }
-    for (; i < n; i += stride) {
-      const C<R> pv = Store<R, T>::ld(p + i);
-      lgt::st<R>(x + i, ld<R>(x + i) + a * pv);
-      if (upd) {
-        const C<R> rv = ld<R>(r + i);
-        Store<R, T>::st(p + i, C<R>{rv.re + b * pv.re, rv.im + b * pv.im});
+      for (int j = 0; j < kTrip; ++j) {
+        if (i + j * stride >= ne) continue;
+#pragma unroll
+        for (int q = 0; q < E::W; ++q) {
+          xv[j][q] += a * pv[j][q];
+          pv[j][q] = C<R>{rv[j][q].re + b * pv[j][q].re, rv[j][q].im + b * pv[j][q].im};
+        }
+        E::st_x(x, i + j * stride, vs, xv[j]);
+        if (upd) E::st_p(p, i + j * stride, pv[j]);
       }
     }
   }
@@ -308,8 +345,9 @@ __global__ __launch_bounds__(256) void k_cg_step(int n, int nblk, const double* 
 }
 
 template <typename R, typename T>
-hipError_t launch_cg_step(int n, const R2<R>* r, T* p, SolverState* st, Reduce red, int nblk, hipStream_t s,
+hipError_t launch_cg_step(int vs, const R2<R>* r, T* p, SolverState* st, Reduce red, int nblk, hipStream_t s,
                           R2<R>* x) {
+  const int n = 12 * vs;
   if (nblk > red.capacity) return hipErrorInvalidValue;
   // each block also sums the nblk partials (a few thousand on large
   // lattices).  With 8-byte elements (FP32, BF16 pairs) a grid of about four
@@ -319,7 +357,7 @@ hipError_t launch_cg_step(int n, const R2<R>* r, T* p, SolverState* st, Reduce r
   // blocks), which is faster for them at 16^4 (6.3 against 7.1 us).
   const int nb = sizeof(R) == 4 ? std::max(1, std::min((n + 1023) / 1024, 1024))
                                 : std::max(1, std::min((n + 255) / 256, 2048));
-  hipLaunchKernelGGL((k_cg_step<R, T>), dim3(nb), dim3(256), 0, s, n, nblk, red.partials, r, p, st, red.mbox, x);
+  hipLaunchKernelGGL((k_cg_step<R, T>), dim3(nb), dim3(256), 0, s, n, vs, nblk, red.partials, r, p, st, red.mbox, x);
   return hipGetLastError();
 }
 template hipError_t launch_cg_step<double, double2>(int, const double2*, double2*, SolverState*, Reduce, int,
@@ -416,7 +454,8 @@ hipError_t launch_convert_64_32(int n, const double2* x, float2* y, hipStream_t 
   return hipGetLastError();
 }
 
-// Two-row copy of a packed link field ([2][4][9][vs] -> [2][4][6][vs]) and
+// Two-row copy of a packed link field ([2][4][9][vs] -> six complex planes a
+// link in FP64, three planes of two in FP32, see load_two_rows) and
 // the check that the links are SU(3): flag is set when a stored third row
 // differs from the conjugate cross product of the first two by more than tol
 // (per component, |re| + |im|), or is not finite.
@@ -431,12 +470,19 @@ __global__ __launch_bounds__(256) void k_compress_links(int vh, int vs, const R2
   if (t >= 8 * vh) return;
   const int pm = t / vh, cb = t - pm * vh;
   const R2<R>* src = U + (size_t)pm * 9 * vs + cb;
-  R2<R>* dst = Uc + (size_t)pm * 6 * vs + cb;
   C<R> m[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) m[k] = ld<R>(src + (size_t)k * vs);
+  if constexpr (sizeof(R) == 8) {
+    R2<R>* dst = Uc + (size_t)pm * 6 * vs + cb;
 #pragma unroll
-  for (int k = 0; k < 6; ++k) st<R>(dst + (size_t)k * vs, m[k]);
+    for (int k = 0; k < 6; ++k) st<R>(dst + (size_t)k * vs, m[k]);
+  } else {
+    v4f32* dst = reinterpret_cast<v4f32*>(Uc) + (size_t)pm * 3 * vs + cb;
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      dst[(size_t)k * vs] = v4f32{m[2 * k].re, m[2 * k].im, m[2 * k + 1].re, m[2 * k + 1].im};
+  }
   const C<R> r6 = conj(m[1] * m[5] - m[2] * m[4]);
   const C<R> r7 = conj(m[2] * m[3] - m[0] * m[5]);
   const C<R> r8 = conj(m[0] * m[4] - m[1] * m[3]);
@@ -456,21 +502,31 @@ hipError_t launch_compress_links(const Geom& g, const double2* U64, double2* Uc,
   return hipGetLastError();
 }
 
+// Between FP64 and FP32 (or BF16) fields: a thread takes the four spins of a
+// colour, blockIdx.y, at a site (see Planes).
+static inline dim3 colour_grid(int vs) { return dim3((vs + 255) / 256, 3); }
+
 // x (FP64) += scale * xs (FP32); xs = 0
-__global__ __launch_bounds__(256) void k_mixed_fold(int n, float2* xs, double2* __restrict__ x,
+__global__ __launch_bounds__(256) void k_mixed_fold(int vs, float2* xs, double2* __restrict__ x,
                                                     const SolverState* st) {
+  const int i = blockIdx.x * 256 + threadIdx.x, own = blockIdx.y;
+  if (i >= vs) return;
   const double scale = 1.0 / st->sigma;
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-    const float2 v = xs[i];
-    double2 xv = x[i];
-    xv.x += scale * (double)v.x;
-    xv.y += scale * (double)v.y;
-    x[i] = xv;
-    xs[i] = make_float2(0.f, 0.f);
+  C<float> v[4];
+  C<double> xv[4];
+  Planes<float, float2>::ld(xs, vs, own, i, v);
+  ld_colour(x, vs, own, i, xv);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    xv[q].re += scale * (double)v[q].re;
+    xv[q].im += scale * (double)v[q].im;
+    v[q] = czero<float>();
   }
+  st_colour(x, vs, own, i, xv);
+  Planes<float, float2>::st(xs, vs, own, i, v);
 }
-hipError_t launch_mixed_fold(int n, float2* xs, double2* x, const SolverState* st, hipStream_t s) {
-  hipLaunchKernelGGL(k_mixed_fold, dim3((n + 255) / 256), dim3(256), 0, s, n, xs, x, st);
+hipError_t launch_mixed_fold(int vs, float2* xs, double2* x, const SolverState* st, hipStream_t s) {
+  hipLaunchKernelGGL(k_mixed_fold, colour_grid(vs), dim3(256), 0, s, vs, xs, x, st);
   return hipGetLastError();
 }
 
@@ -515,51 +571,65 @@ hipError_t launch_reliable_decide(int n, const double2* r64, Reduce red, SolverS
 // to unit norm), and the search direction either restarted (p = r) or
 // rescaled to the new units (p *= pscale).
 template <typename T>
-__global__ __launch_bounds__(256) void k_rescale_residual(int n, const double2* __restrict__ r64, double sigma,
-                                                          float2* __restrict__ r, T* __restrict__ p, int restart,
-                                                          double bscale) {
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-    const double2 v = r64[i];
-    const double rx = sigma * v.x, ry = sigma * v.y;
-    st<float>(r + i, C<float>{(float)rx, (float)ry});
-    if (restart) {
-      Store<float, T>::st(p + i, C<float>{(float)rx, (float)ry});
-    } else {
-      const C<float> q = Store<float, T>::ld(p + i);
-      Store<float, T>::st(p + i, C<float>{(float)(rx + bscale * (double)q.re), (float)(ry + bscale * (double)q.im)});
-    }
+__device__ __forceinline__ void rescale_site(int vs, const double2* __restrict__ r64, double sigma,
+                                             float2* __restrict__ r, T* __restrict__ p, bool restart, double bscale) {
+  const int i = blockIdx.x * 256 + threadIdx.x, own = blockIdx.y;
+  if (i >= vs) return;
+  C<double> v[4];
+  C<float> rv[4], pv[4];
+  ld_colour(r64, vs, own, i, v);
+  if (!restart) Planes<float, T>::ld(p, vs, own, i, pv);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double rx = sigma * v[q].re, ry = sigma * v[q].im;
+    rv[q] = {(float)rx, (float)ry};
+    pv[q] = restart ? rv[q]
+                    : C<float>{(float)(rx + bscale * (double)pv[q].re), (float)(ry + bscale * (double)pv[q].im)};
   }
+  Planes<float, float2>::st(r, vs, own, i, rv);
+  Planes<float, T>::st(p, vs, own, i, pv);
 }
 template <typename T>
-hipError_t launch_rescale_residual(int n, const double2* r64, double sigma, float2* r, T* p, int restart,
+__global__ __launch_bounds__(256) void k_rescale_residual(int vs, const double2* __restrict__ r64, double sigma,
+                                                          float2* __restrict__ r, T* __restrict__ p, int restart,
+                                                          double bscale) {
+  rescale_site(vs, r64, sigma, r, p, restart != 0, bscale);
+}
+template <typename T>
+hipError_t launch_rescale_residual(int vs, const double2* r64, double sigma, float2* r, T* p, int restart,
                                    double bscale, hipStream_t s) {
-  hipLaunchKernelGGL((k_rescale_residual<T>), dim3((n + 255) / 256), dim3(256), 0, s, n, r64, sigma, r, p, restart,
-                     bscale);
+  hipLaunchKernelGGL((k_rescale_residual<T>), colour_grid(vs), dim3(256), 0, s, vs, r64, sigma, r, p, restart, bscale);
   return hipGetLastError();
 }
 template <typename T>
-__global__ __launch_bounds__(256) void k_rescale_residual_dev(int n, const double2* __restrict__ r64,
+__global__ __launch_bounds__(256) void k_rescale_residual_dev(int vs, const double2* __restrict__ r64,
                                                               float2* __restrict__ r, T* __restrict__ p,
                                                               const SolverState* state) {
   if (state->done != kDoneRunning) return;
-  const double sigma = state->sigma, bscale = state->bscale;
-  const int restart = state->restart;
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-    const double2 v = r64[i];
-    const double rx = sigma * v.x, ry = sigma * v.y;
-    st<float>(r + i, C<float>{(float)rx, (float)ry});
-    if (restart) {
-      Store<float, T>::st(p + i, C<float>{(float)rx, (float)ry});
-    } else {
-      const C<float> q = Store<float, T>::ld(p + i);
-      Store<float, T>::st(p + i, C<float>{(float)(rx + bscale * (double)q.re), (float)(ry + bscale * (double)q.im)});
-    }
-  }
+  rescale_site(vs, r64, state->sigma, r, p, state->restart != 0, state->bscale);
 }
 template <typename T>
-hipError_t launch_rescale_residual_dev(int n, const double2* r64, float2* r, T* p, const SolverState* st,
+hipError_t launch_rescale_residual_dev(int vs, const double2* r64, float2* r, T* p, const SolverState* st,
                                        hipStream_t s) {
-  hipLaunchKernelGGL((k_rescale_residual_dev<T>), dim3((n + 255) / 256), dim3(256), 0, s, n, r64, r, p, st);
+  hipLaunchKernelGGL((k_rescale_residual_dev<T>), colour_grid(vs), dim3(256), 0, s, vs, r64, r, p, st);
+  return hipGetLastError();
+}
+
+// FP32 copy of nr FP64 half fields in the batched layout (nr = 1: a half field)
+__global__ __launch_bounds__(256) void k_half_64_32(int vs, int nr, const double2* __restrict__ x,
+                                                    float2* __restrict__ y) {
+  const int i = blockIdx.x * 256 + threadIdx.x, own = blockIdx.y / nr, n = blockIdx.y % nr;
+  if (i >= vs) return;
+  const size_t ps = (size_t)nr * vs, o = (size_t)n * vs + i;
+  C<double> v[4];
+  C<float> w[4];
+  ld_colour(x, ps, own, o, v);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) w[q] = cvt<float>(v[q]);
+  Planes<float, float2>::st(y, ps, own, o, w);
+}
+hipError_t launch_half_64_32(int vs, int nr, const double2* x, float2* y, hipStream_t s) {
+  hipLaunchKernelGGL(k_half_64_32, dim3((vs + 255) / 256, 3 * nr), dim3(256), 0, s, vs, nr, x, y);
   return hipGetLastError();
 }
 template hipError_t launch_rescale_residual_dev<float2>(int, const double2*, float2*, float2*, const SolverState*,
@@ -574,8 +644,6 @@ template hipError_t launch_rescale_residual<Bf16c>(int, const double2*, double, 
 
 template hipError_t launch_cg_init<double>(int, const double2*, double2*, double2*, double2*, SolverState*,
                                            Reduce, double, int, hipStream_t);
-template hipError_t launch_cg_init<float>(int, const float2*, float2*, float2*, float2*, SolverState*, Reduce,
-                                          double, int, hipStream_t);
 
 
 }  // namespace lgt

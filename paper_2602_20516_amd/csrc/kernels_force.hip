@@ -102,9 +102,7 @@ __device__ __forceinline__ M3<double> bilinear_z(const double2 (*sa)[kSB], const
   for (int k = 0; k < 9; ++k) Z.m[k] = czero<double>();
   C<double> psi[12], hx[6], hy[6];
   {  // h-[b(x+mu)] h-[a(x)]^dag
-    const unsigned ob = b_nb.off(nf, 0);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) psi[k] = b_nb.ld(ob, k);
+    b_nb.all(b_nb.off(nf), psi);
     project<double, MU, -1>(psi, hx);
 #pragma unroll
     for (int k = 0; k < 12; ++k) psi[k] = cmk<double>(sa[k][lane].x, sa[k][lane].y);
@@ -115,9 +113,7 @@ __device__ __forceinline__ M3<double> bilinear_z(const double2 (*sa)[kSB], const
       for (int j = 0; j < 3; ++j) Z.m[3 * i + j] += mulcj(hx[i], hy[j]) + mulcj(hx[3 + i], hy[3 + j]);
   }
   {  // h+[a(x+mu)] h+[b(x)]^dag
-    const unsigned oa = a_nb.off(nf, 0);
-#pragma unroll
-    for (int k = 0; k < 12; ++k) psi[k] = a_nb.ld(oa, k);
+    a_nb.all(a_nb.off(nf), psi);
     project<double, MU, +1>(psi, hx);
 #pragma unroll
     for (int k = 0; k < 12; ++k) psi[k] = cmk<double>(sb[k][lane].x, sb[k][lane].y);
@@ -175,9 +171,8 @@ __global__ __launch_bounds__(256) void k_bilinear_sb(Geom g, const double2* __re
   int c[4];
   cb_coords(g, p, active ? cb : 0, c);
   const int nf = cb_shift(g, c, mu, +1);
-  const unsigned ks = (unsigned)g.vs * (unsigned)sizeof(double2);
-  const SpinorIn<double, double2> a_nb{make_rsrc(a + (1 - p) * half, (size_t)12 * ks), ks, 1u};
-  const SpinorIn<double, double2> b_nb{make_rsrc(b + (1 - p) * half, (size_t)12 * ks), ks, 1u};
+  const auto a_nb = make_spinor_in<double>(a + (1 - p) * half, g);
+  const auto b_nb = make_spinor_in<double>(b + (1 - p) * half, g);
   __syncthreads();
   M3<double> Z;
   switch (mu) {
@@ -246,7 +241,6 @@ __global__ __launch_bounds__(256) void k_bilinear_sum(Geom g, const double2* __r
   int c[4];
   cb_coords(g, p, cbx, c);
   const int nf = cb_shift(g, c, mu, +1);
-  const unsigned ks = (unsigned)g.vs * (unsigned)sizeof(double2);
   double2* zl = zsum + (size_t)((p * 4 + mu) * 9) * g.vs + cbx;
   M3<double> Z;
 #pragma unroll
@@ -266,8 +260,8 @@ __global__ __launch_bounds__(256) void k_bilinear_sum(Geom g, const double2* __r
       if (site < g.vh) v = (f ? bp : ap)[(size_t)k * g.vs + site];
       (f ? sb : sa)[k][l] = make_double2(wt * v.x, wt * v.y);
     }
-    const SpinorIn<double, double2> a_nb{make_rsrc(an, (size_t)12 * ks), ks, 1u};
-    const SpinorIn<double, double2> b_nb{make_rsrc(bn, (size_t)12 * ks), ks, 1u};
+    const auto a_nb = make_spinor_in<double>(an, g);
+    const auto b_nb = make_spinor_in<double>(bn, g);
     __syncthreads();
     M3<double> z;
     switch (mu) {

@@ -11,9 +11,10 @@
 // hops along mu for the 64 sites, using the chiral-basis spin projection
 // (1 + s gamma_mu) psi = (h ; s B_mu^dag h), h = psi_up + s B_mu psi_dn, so
 // only two colour vectors go through each SU(3) multiply.  The four
-// per-direction partial spinors meet in LDS and wave w then owns spin
-// component w of the 64 output sites for the epilogue, so every global load
-// and store is a unit-stride 64-lane access in the [12][vh] SoA layout.
+// per-direction partial spinors meet in LDS and wave w then owns a part of the
+// components of the 64 output sites for the epilogue (see Planes: spin w in
+// FP64, colour w otherwise), so every global load and store is a unit-stride
+// access of 16 bytes a lane.
 // Small lattices use 32-site blocks instead, whose half-waves take the
 // forward and the backward hop (unit-stride 32-lane halves).
 // Blocks are numbered XCD-contiguously (see xcd_block).
@@ -23,10 +24,10 @@
 namespace lgt {
 
 // ---------------------------------------------------------------------------
-// Epilogues.  apply() gets the 3 colour components of spin `spin` of the hop
-// result at (p, cb); red accumulates this thread's reduction contribution.
+// Epilogues.  apply() gets the components of owner `own` of the hop result at
+// (p, cb) (see Planes); red accumulates this thread's reduction contribution.
 // T is the storage type of the spinors t, w, p of the CG (R2<R> or Bf16c);
-// x and r are always R2<R>.
+// x and r are always R2<R>, with the same owners.  vh: plane stride.
 // ---------------------------------------------------------------------------
 template <typename R, typename T>
 struct EpiAxpy {  // out = self + coef * acc
@@ -43,22 +44,21 @@ struct EpiAxpy {  // out = self + coef * acc
   const double* pap_partials;
   int pap_nblk;
   __device__ bool skip() const { return guard && guard->done != kDoneRunning; }
+  using P = Planes<R, T>;
+  static constexpr int NC = P::NC;
   struct Pre {
-    C<R> s[3];
+    C<R> s[NC];
   };
-  __device__ Pre pre(int p, int cb, int spin) const {
-    Pre q;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-      q.s[i] = self[p] ? Store<R, T>::ld(self[p] + (size_t)(3 * spin + i) * vh + cb) : czero<R>();
+  __device__ Pre pre(int p, int cb, int own) const {
+    Pre q{};
+    if (self[p]) P::ld(self[p], vh, own, cb, q.s);
     return q;
   }
-  __device__ void apply(int p, int cb, int spin, const C<R>* acc, double&, const Pre& q) const {
+  __device__ void apply(int p, int cb, int own, const C<R>* acc, double&, const Pre& q) const {
+    C<R> v[NC];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const size_t o = (size_t)(3 * spin + i) * vh + cb;
-      Store<R, T>::st(out[p] + o, q.s[i] + coef * acc[i]);
-    }
+    for (int i = 0; i < NC; ++i) v[i] = q.s[i] + coef * acc[i];
+    P::st(out[p], vh, own, cb, v);
   }
   template <int NT>
   __device__ void tail() const {
@@ -146,28 +146,28 @@ struct EpiStep {
     __syncthreads();
     return !s_run;
   }
+  using P = Planes<R, R2<R>>;
+  static constexpr int NC = P::NC;
   struct Pre {
-    C<R> t[3], r[3], p[3];
+    C<R> t[NC], r[NC], p[NC];
   };
-  __device__ Pre pre(int, int cb, int spin) const {
+  __device__ Pre pre(int, int cb, int own) const {
     Pre q;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const size_t o = (size_t)(3 * spin + i) * vh + cb;
-      q.t[i] = ld<R>(t + o);
-      q.r[i] = ld<R>(r + o);
-      q.p[i] = ld<R>(p + o);
-    }
+    P::ld(t, vh, own, cb, q.t);
+    P::ld(r, vh, own, cb, q.r);
+    P::ld(p, vh, own, cb, q.p);
     return q;
   }
-  __device__ void apply(int, int cb, int spin, const C<R>* acc, double&, const Pre& q) const {
+  __device__ void apply(int, int cb, int own, const C<R>* acc, double&, const Pre& q) const {
     const R b = R(beta_sh());
+    C<R> tn[NC], pn[NC];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const size_t o = (size_t)(3 * spin + i) * vh + cb;
-      lgt::st<R>(t + o, acc[i] + b * q.t[i]);
-      lgt::st<R>(p + o, q.r[i] + b * q.p[i]);
+    for (int i = 0; i < NC; ++i) {
+      tn[i] = acc[i] + b * q.t[i];
+      pn[i] = q.r[i] + b * q.p[i];
     }
+    P::st(t, vh, own, cb, tn);
+    P::st(p, vh, own, cb, pn);
   }
   template <int NT>
   __device__ void tail() const {}
@@ -177,6 +177,7 @@ struct EpiStep {
 // p = r + beta p as in EpiStep, with beta and the stop decision from the
 // state, where the finalize that advances the shifts has left them.
 struct EpiDirection {
+  using P = Planes<double, double2>;
   static constexpr bool kReduce = false;
   static constexpr bool kPrefetch = true;
   double2* t;
@@ -215,6 +216,7 @@ struct EpiDirection {
 // Last hop of a shifted true residual: block partials of
 // |phi - (w + coef * acc) - sigma x|^2 (odd sites); nothing is stored.
 struct EpiShiftResidual {
+  using P = Planes<double, double2>;
   static constexpr bool kReduce = true;
   static constexpr bool kPrefetch = true;
   const double2* w;
@@ -255,23 +257,24 @@ struct EpiSchurNorm {  // w = x + coef * acc (odd sites), block partials of |w|^
   int vh;
   SolverState* state;
   __device__ bool skip() const { return state->done != kDoneRunning; }
+  using P = Planes<R, T>;
+  static constexpr int NC = P::NC;
   struct Pre {
-    C<R> x[3];
+    C<R> x[NC];
   };
-  __device__ Pre pre(int, int cb, int spin) const {
+  __device__ Pre pre(int, int cb, int own) const {
     Pre q;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) q.x[i] = Store<R, T>::ld(x + (size_t)(3 * spin + i) * vh + cb);
+    P::ld(x, vh, own, cb, q.x);
     return q;
   }
-  __device__ void apply(int, int cb, int spin, const C<R>* acc, double& red, const Pre& q) const {
+  __device__ void apply(int, int cb, int own, const C<R>* acc, double& red, const Pre& q) const {
+    C<R> v[NC];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const size_t o = (size_t)(3 * spin + i) * vh + cb;
-      const C<R> v = Store<R, T>::round(q.x[i] + coef * acc[i]);
-      Store<R, T>::st(w + o, v);
-      red += (double)v.re * (double)v.re + (double)v.im * (double)v.im;
+    for (int i = 0; i < NC; ++i) {
+      v[i] = Store<R, T>::round(q.x[i] + coef * acc[i]);
+      red += (double)v[i].re * (double)v[i].re + (double)v[i].im * (double)v[i].im;
     }
+    P::st(w, vh, own, cb, v);
   }
   template <int NT>
   __device__ void tail() const {}
@@ -290,40 +293,44 @@ struct EpiSchurCG {  // q = w + coef * acc; x += alpha p (if x); ro = r - alpha 
   int vh;
   SolverState* state;
   __device__ bool skip() const { return state->done != kDoneRunning; }
+  using P = Planes<R, T>;        // w, p
+  using PR = Planes<R, R2<R>>;   // x, r
+  static constexpr int NC = P::NC;
   struct Pre {
-    C<R> w[3], x[3], r[3], p[3];
+    C<R> w[NC], x[NC], r[NC], p[NC];
   };
-  __device__ Pre pre(int, int cb, int spin) const {
+  __device__ Pre pre(int, int cb, int own) const {
     Pre q;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const size_t o = (size_t)(3 * spin + i) * vh + cb;
-      q.w[i] = Store<R, T>::ld(w + o);
-      q.r[i] = ld<R>(r + o);
-      if (x) {
-        q.x[i] = ld<R>(x + o);
-        q.p[i] = Store<R, T>::ld(p + o);
-      }
+    P::ld(w, vh, own, cb, q.w);
+    PR::ld(r, vh, own, cb, q.r);
+    if (x) {
+      PR::ld(x, vh, own, cb, q.x);
+      P::ld(p, vh, own, cb, q.p);
     }
     return q;
   }
-  __device__ void apply(int, int cb, int spin, const C<R>* acc, double& red, const Pre& pq) const {
+  __device__ void apply(int, int cb, int own, const C<R>* acc, double& red, const Pre& pq) const {
     const R alpha = R(state->alpha);
+    C<R> rv[NC], xv[NC];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const size_t o = (size_t)(3 * spin + i) * vh + cb;
+    for (int i = 0; i < NC; ++i) {
       const C<R> q = pq.w[i] + coef * acc[i];
-      if (x) st<R>(x + o, pq.x[i] + alpha * pq.p[i]);
-      C<R> rv = pq.r[i] - alpha * q;
-      st<R>(ro + o, rv);
-      red += (double)rv.re * (double)rv.re + (double)rv.im * (double)rv.im;
+      rv[i] = pq.r[i] - alpha * q;
+      red += (double)rv[i].re * (double)rv[i].re + (double)rv[i].im * (double)rv[i].im;
     }
+    if (x) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) xv[i] = pq.x[i] + alpha * pq.p[i];
+      PR::st(x, vh, own, cb, xv);
+    }
+    PR::st(ro, vh, own, cb, rv);
   }
   template <int NT>
   __device__ void tail() const {}
 };
 
 struct EpiResidual {  // r = phi - (self + coef * acc) over both parities, block partials of |r|^2
+  using P = Planes<double, double2>;
   static constexpr bool kReduce = true;
   static constexpr bool kPrefetch = true;
   const double2* self[2];
@@ -377,11 +384,30 @@ struct EpiResidual {  // r = phi - (self + coef * acc) over both parities, block
 // of a chunk are a few blocks apart and its z-hops 8 tgrp blocks apart.  A
 // bijection of the blocks of a parity: every site is still covered once.
 // ---------------------------------------------------------------------------
+// A wave's partial hops in its part of the LDS, in the planes of a half field
+// of 64 sites, and an owner's part of them back.
+template <typename R>
+__device__ __forceinline__ void put_hops(R2<R>* l, int lane, const C<R>* acc) {
+  using P = Planes<R, R2<R>>;
+#pragma unroll
+  for (int own = 0; own < P::kOwners; ++own) {
+    C<R> v[P::NC];
+#pragma unroll
+    for (int q = 0; q < P::NC; ++q) v[q] = acc[P::comp(own, q)];
+    P::st(l, 64, own, lane, v);
+  }
+}
+template <typename R>
+__device__ __forceinline__ void get_hops(const R2<R>* l, int lane, int own, C<R>* v) {
+  Planes<R, R2<R>>::ld(l, 64, own, lane, v);
+}
+
 template <typename R, bool DAG, typename Epi, typename In, int NS>
 __global__ __launch_bounds__(256) void k_hop(Geom g, int nbp, int p_fixed, In hin, Epi epi, double* partials,
                                              int bps, int tgrp) {
   static_assert(NS == 64 || NS == 32, "64 or 32 sites per block");
   if (epi.skip()) return;
+  using P = typename Epi::P;
   __shared__ R2<R> lds[4][12][64];
   const int lb = xcd_block(blockIdx.x, gridDim.x);
   const int p = p_fixed >= 0 ? p_fixed : lb / nbp;
@@ -405,7 +431,7 @@ __global__ __launch_bounds__(256) void k_hop(Geom g, int nbp, int p_fixed, In hi
   // (24^3x48: 65.0 -> 67.5 ms).
   typename Epi::Pre pre{};
   if constexpr (NS == 64 && Epi::kPrefetch) {
-    if (active) pre = epi.pre(p, cb, mu);
+    if (active && mu < P::kOwners) pre = epi.pre(p, cb, mu);
   }
 
   C<R> acc[12];
@@ -414,13 +440,13 @@ __global__ __launch_bounds__(256) void k_hop(Geom g, int nbp, int p_fixed, In hi
   if (active) {
     int c[4];
     cb_coords(g, p, cb, c);
-    const auto in = make_loader<R>(hin, g, p, 1);
+    const auto in = make_loader<R>(hin, g, p);
     if constexpr (NS == 64) {
       switch (mu) {
-        case 0: hop_dir<R, 0, DAG>(g, hin.gauge, hin.nk, in, p, cb, c, acc, 0); break;
-        case 1: hop_dir<R, 1, DAG>(g, hin.gauge, hin.nk, in, p, cb, c, acc, 0); break;
-        case 2: hop_dir<R, 2, DAG>(g, hin.gauge, hin.nk, in, p, cb, c, acc, 0); break;
-        default: hop_dir<R, 3, DAG>(g, hin.gauge, hin.nk, in, p, cb, c, acc, 0); break;
+        case 0: hop_dir<R, 0, DAG>(g, hin.gauge, hin.nk, in, p, cb, c, acc); break;
+        case 1: hop_dir<R, 1, DAG>(g, hin.gauge, hin.nk, in, p, cb, c, acc); break;
+        case 2: hop_dir<R, 2, DAG>(g, hin.gauge, hin.nk, in, p, cb, c, acc); break;
+        default: hop_dir<R, 3, DAG>(g, hin.gauge, hin.nk, in, p, cb, c, acc); break;
       }
     } else {
       switch (mu) {
@@ -431,48 +457,43 @@ __global__ __launch_bounds__(256) void k_hop(Geom g, int nbp, int p_fixed, In hi
       }
     }
   }
-#pragma unroll
-  for (int k = 0; k < 12; ++k) {
-    R2<R> v;
-    v.x = acc[k].re;
-    v.y = acc[k].im;
-    lds[mu][k][lane] = v;
-  }
+  put_hops<R>(&lds[mu][0][0], lane, acc);
   __syncthreads();
   double red = 0.0;
   if constexpr (NS == 64) {
-    // wave `mu` now owns spin component `mu` of the 64 sites
-    const int spin = mu;
-    C<R> out[3];
+    // wave `mu` now owns its part of the components of the 64 sites
+    if (mu < P::kOwners) {
+      C<R> out[P::NC], b[P::NC];
+      get_hops<R>(&lds[0][0][0], lane, mu, out);
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const int k = 3 * spin + i;
-      R2<R> a = lds[0][k][lane], b = lds[1][k][lane], cc = lds[2][k][lane], d = lds[3][k][lane];
-      out[i] = cmk<R>(((a.x + b.x) + cc.x) + d.x, ((a.y + b.y) + cc.y) + d.y);
+      for (int m = 1; m < 4; ++m) {
+        get_hops<R>(&lds[m][0][0], lane, mu, b);
+#pragma unroll
+        for (int i = 0; i < P::NC; ++i) out[i] += b[i];
+      }
+      if constexpr (!Epi::kPrefetch) {
+        if (active) pre = epi.pre(p, cb, mu);
+      }
+      if (active) epi.apply(p, cb, mu, out, red, pre);
     }
-    if constexpr (!Epi::kPrefetch) {
-      if (active) pre = epi.pre(p, cb, spin);
-    }
-    if (active) epi.apply(p, cb, spin, out, red, pre);
   } else if (mu < 2) {
-    // lane -> site lane & 31, spin 2 mu + lane / 32; eight partial hops
+    // lane -> site lane & 31, owner 2 mu + lane / 32; eight partial hops
     const int site = lane & 31;
-    const int spin = 2 * mu + (lane >> 5);
+    const int own = 2 * mu + (lane >> 5);
     const int cbo = blk * 32 + site;
-    C<R> out[3];
+    C<R> out[P::NC], f[P::NC], b[P::NC];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const int k = 3 * spin + i;
-      R sx = R(0), sy = R(0);
+    for (int i = 0; i < P::NC; ++i) out[i] = czero<R>();
+    if (own < P::kOwners) {
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
-        const R2<R> f = lds[m][k][site], b = lds[m][k][32 + site];
-        sx += f.x + b.x;
-        sy += f.y + b.y;
+        get_hops<R>(&lds[m][0][0], site, own, f);
+        get_hops<R>(&lds[m][0][0], 32 + site, own, b);
+#pragma unroll
+        for (int i = 0; i < P::NC; ++i) out[i] += f[i] + b[i];
       }
-      out[i] = cmk<R>(sx, sy);
+      if (cbo < g.vh) epi.apply(p, cbo, own, out, red, epi.pre(p, cbo, own));
     }
-    if (cbo < g.vh) epi.apply(p, cbo, spin, out, red, epi.pre(p, cbo, spin));
   }
   if constexpr (Epi::kReduce) {
     double v[1] = {red};

@@ -1,9 +1,10 @@
 // Multi-right-hand-side kernels: nr spinor fields on one lattice, solved
 // together (one pseudofermion per right-hand side, each with its own kappa).
 //
-// Layout of a multi-RHS half field: [12 components][nr][vs] complex (site
-// fastest, planes vs >= V/2 sites apart; their padding holds anything finite
-// or not and is never summed, since it moves with nr), a full field the even half then the odd half.  Every
+// Layout of a multi-RHS half field: the planes of a single half field (see
+// Planes), each [nr][vs] (site fastest, vs >= V/2 sites apart; their padding
+// holds anything, finite or not, and is never summed, since it moves with
+// nr), a full field the even half then the odd half.  Every
 // per-component access of a wave is unit stride, as in the single field.
 //
 // Hop decomposition: a 256-thread block owns 64 consecutive sites of one
@@ -48,14 +49,18 @@ __device__ __forceinline__ double sum_rows(const double* __restrict__ partials, 
 }
 
 // ---------------------------------------------------------------------------
-// Epilogues (element (k, n, cb) of the hop result, offset o).  rhs_active(n)
-// false: nothing of right-hand side n in this launch is used (its CG has
-// stopped: converged, or idle until the next reliable update), so the
-// kernel skips its hop and writes 0 for its partial.
+// Epilogues (owner `own`'s components of right-hand side n at (p, cb), see
+// Planes; ps: plane stride nr vs, i = n vs + cb).  rhs_active(n) false:
+// nothing of right-hand side n in this launch is used (its CG has stopped:
+// converged, or idle until the next reliable update), so the kernel skips its
+// hop and writes 0 for its partial.  pre() loads the other operands; the VALU
+// kernel calls it before the hop, which they do not depend on.
 // ---------------------------------------------------------------------------
 template <typename R>
 struct MEpiAxpy {  // out = self + coef_n * acc
   static constexpr bool kReduce = false;
+  using P = Planes<R, R2<R>>;
+  static constexpr int NC = P::NC;
   R2<R>* out[2];
   const R2<R>* self[2];
   const double* coef;  // [NR] device array
@@ -68,10 +73,19 @@ struct MEpiAxpy {  // out = self + coef_n * acc
   __device__ bool rhs_active(int n) const {
     return (!mask || mask[n] != 0.0) && (!guard || guard->done[n] == kDoneRunning);
   }
-  __device__ void apply(int p, size_t o, int n, C<R> a, double&) const {
-    C<R> v = R(coef[n]) * a;
-    if (self[p]) v += ld<R>(self[p] + o);
-    st<R>(out[p] + o, v);
+  struct Pre {
+    C<R> s[NC];
+  };
+  __device__ Pre pre(int p, size_t ps, int own, size_t i) const {
+    Pre q{};
+    if (self[p]) P::ld(self[p], ps, own, i, q.s);
+    return q;
+  }
+  __device__ void apply(int p, size_t ps, int own, size_t i, int n, const C<R>* a, double&, const Pre& q) const {
+    C<R> v[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) v[k] = R(coef[n]) * a[k] + q.s[k];
+    P::st(out[p], ps, own, i, v);
   }
   __device__ void tail(int nr) const {
     if (!pap_partials || blockIdx.x != 0) return;
@@ -92,75 +106,118 @@ struct MEpiAxpy {  // out = self + coef_n * acc
 template <typename R>
 struct MEpiSchurNorm {  // w = x + coef_n acc, per-RHS |w|^2
   static constexpr bool kReduce = true;
+  using P = Planes<R, R2<R>>;
+  static constexpr int NC = P::NC;
   R2<R>* w;
   const R2<R>* x;
   const double* coef;
   const BatchState* state;
   __device__ bool skip() const { return state->all_done; }
   __device__ bool rhs_active(int n) const { return state->done[n] == kDoneRunning; }
-  __device__ void apply(int, size_t o, int n, C<R> a, double& red) const {
-    const C<R> v = ld<R>(x + o) + R(coef[n]) * a;
-    st<R>(w + o, v);
-    red += (double)v.re * (double)v.re + (double)v.im * (double)v.im;
+  struct Pre {
+    C<R> x[NC];
+  };
+  __device__ Pre pre(int, size_t ps, int own, size_t i) const {
+    Pre q;
+    P::ld(x, ps, own, i, q.x);
+    return q;
+  }
+  __device__ void apply(int, size_t ps, int own, size_t i, int n, const C<R>* a, double& red, const Pre& q) const {
+    C<R> v[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      v[k] = q.x[k] + R(coef[n]) * a[k];
+      red += (double)v[k].re * (double)v[k].re + (double)v[k].im * (double)v[k].im;
+    }
+    P::st(w, ps, own, i, v);
   }
   __device__ void tail(int) const {}
 };
 
 template <typename R>
-struct MEpiSchurCG {  // q = w + coef_n acc; r -= alpha_n q (unless converged); x += alpha_n p if x is set
+struct MEpiSchurCG {  // q = w + coef_n acc; r -= alpha_n q (unless converged)
   static constexpr bool kReduce = true;
+  using P = Planes<R, R2<R>>;
+  static constexpr int NC = P::NC;
   const R2<R>* w;
-  R2<R>* x;
   R2<R>* r;
-  const R2<R>* p;
   const double* coef;
   const BatchState* state;
   __device__ bool skip() const { return state->all_done; }
   __device__ bool rhs_active(int n) const { return state->done[n] == kDoneRunning; }
-  __device__ void apply(int, size_t o, int n, C<R> a, double& red) const {
-    C<R> rv = ld<R>(r + o);
-    if (!state->done[n]) {
-      const R alpha = R(state->alpha[n]);
-      const C<R> q = ld<R>(w + o) + R(coef[n]) * a;
-      if (x) st<R>(x + o, ld<R>(x + o) + alpha * ld<R>(p + o));
-      rv = rv - alpha * q;
-      st<R>(r + o, rv);
+  struct Pre {
+    C<R> r[NC], w[NC];
+  };
+  __device__ Pre pre(int, size_t ps, int own, size_t i) const {
+    Pre q;
+    P::ld(r, ps, own, i, q.r);
+    P::ld(w, ps, own, i, q.w);
+    return q;
+  }
+  __device__ void apply(int, size_t ps, int own, size_t i, int n, const C<R>* a, double& red, const Pre& q) const {
+    const bool run = !state->done[n];
+    const R alpha = R(state->alpha[n]);
+    C<R> rv[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      rv[k] = q.r[k];
+      if (run) rv[k] = rv[k] - alpha * (q.w[k] + R(coef[n]) * a[k]);
+      red += (double)rv[k].re * (double)rv[k].re + (double)rv[k].im * (double)rv[k].im;
     }
-    red += (double)rv.re * (double)rv.re + (double)rv.im * (double)rv.im;
+    if (run) P::st(r, ps, own, i, rv);
   }
   __device__ void tail(int) const {}
 };
 
 struct MEpiResidual {  // r = phi - (self + coef_n acc), per-RHS |r|^2 (both parities, FP64)
   static constexpr bool kReduce = true;
+  using P = Planes<double, double2>;
+  static constexpr int NC = P::NC;
   const double2* self[2];
   const double2* phi[2];
   double2* r[2];
   const double* coef;
   __device__ bool skip() const { return false; }
   __device__ bool rhs_active(int) const { return true; }
-  __device__ void apply(int p, size_t o, int n, C<double> a, double& red) const {
-    const C<double> v = ld<double>(phi[p] + o) - (ld<double>(self[p] + o) + coef[n] * a);
-    st<double>(r[p] + o, v);
-    red += norm2(v);
+  struct Pre {
+    C<double> f[NC], s[NC];
+  };
+  __device__ Pre pre(int p, size_t ps, int own, size_t i) const {
+    Pre q;
+    P::ld(phi[p], ps, own, i, q.f);
+    P::ld(self[p], ps, own, i, q.s);
+    return q;
+  }
+  __device__ void apply(int p, size_t ps, int own, size_t i, int n, const C<double>* a, double& red,
+                        const Pre& q) const {
+    C<double> v[NC];
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      v[k] = q.f[k] - (q.s[k] + coef[n] * a[k]);
+      red += norm2(v[k]);
+    }
+    P::st(r[p], ps, own, i, v);
   }
   __device__ void tail(int) const {}
 };
 
 
-// Loader of one right-hand side of a multi-RHS field: element (k, n, site)
-// at (k*nr + n)*vs + site; the per-lane offset carries site and n, the
-// component offset is uniform.
+// Loader of one right-hand side of a multi-RHS field: a plane is [nr][vs]
+// vectors of 16 bytes; the per-lane offset carries site and n, the plane
+// offset is uniform.
 template <typename R>
 struct MrhsIn {
   BufRsrc rs;
-  unsigned ks;  // component stride in bytes (nr * vs elements)
-  unsigned ns;  // right-hand-side stride in bytes (vs elements)
-  __device__ __forceinline__ unsigned off(int site, int n) const {
-    return (unsigned)site * (unsigned)sizeof(R2<R>) + (unsigned)n * ns;
-  }
-  __device__ __forceinline__ C<R> ld(unsigned o, int k) const { return ld_buf<R>(rs, o, k * ks); }
+  unsigned ks;  // plane stride in bytes (nr * vs vectors)
+  unsigned ns;  // right-hand-side stride in bytes (vs vectors)
+  __device__ __forceinline__ unsigned off(int site, int n) const { return (unsigned)site * 16u + (unsigned)n * ns; }
+  __device__ __forceinline__ void all(unsigned o, C<R>* psi) const { Planes<R, R2<R>>::all(rs, o, ks, psi); }
 };
+template <typename R>
+__device__ __forceinline__ MrhsIn<R> make_mrhs_in(const R2<R>* half, const Geom& g, int nr) {
+  const unsigned ns = (unsigned)g.vs * 16u, ks = (unsigned)nr * ns;
+  return {make_rsrc(half, (size_t)Planes<R, R2<R>>::kPlanes * ks), ks, ns};
+}
 
 // wave-level sum in a fixed butterfly order (all 64 lanes get the total)
 __device__ __forceinline__ double wave_sum(double v) {
@@ -169,11 +226,41 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// The partial hops of wave MU for the other owners: strip [owner][source] of
+// the exchange, the source counted without the owner's own wave, which keeps
+// its part in registers.
+template <typename R>
+struct Exchange {
+  using P = Planes<R, R2<R>>;
+  static constexpr int kStrip = P::NC * 64;  // R2<R> of an owner's part for 64 sites
+  static constexpr int kSize = P::kOwners * 3 * kStrip;
+  static __device__ __forceinline__ R2<R>* strip(R2<R>* ex, int own, int src) { return ex + (own * 3 + src) * kStrip; }
+  // place (0, plane q) of a strip: an owner's planes, 64 vectors each
+  template <int MU>
+  static __device__ __forceinline__ void share(const C<R>* acc, R2<R>* ex, int lane, C<R>* mine) {
+#pragma unroll
+    for (int own = 0; own < P::kOwners; ++own) {
+      C<R> v[P::NC];
+#pragma unroll
+      for (int q = 0; q < P::NC; ++q) v[q] = acc[P::comp(own, q)];
+      if (own == MU) {
+#pragma unroll
+        for (int q = 0; q < P::NC; ++q) mine[q] = v[q];
+      } else {
+        P::st(strip(ex, own, MU < own ? MU : MU - 1), 64, 0, lane, v);
+      }
+    }
+  }
+};
+
 template <typename R, bool DAG, typename Epi>
 __global__ __launch_bounds__(256) void k_hop_mrhs(Geom g, int nr, int G, int nbp, int ngrp, int p_fixed,
                                                   HopIn<R> hin, Epi epi, double* partials) {
   if (epi.skip()) return;
-  __shared__ R2<R> lds[4][12][64];
+  // two buffers, so that one barrier a right-hand side is enough
+  using P = typename Epi::P;
+  using X = Exchange<R>;
+  __shared__ __align__(16) R2<R> lds[2][X::kSize];
   __shared__ double wred[4][kMaxRhs];
   const int lb = xcd_block(blockIdx.x, gridDim.x);
   const int per_par = nbp * ngrp;
@@ -199,8 +286,8 @@ __global__ __launch_bounds__(256) void k_hop_mrhs(Geom g, int nr, int G, int nbp
   const unsigned act = s_act;
   constexpr unsigned E = sizeof(R2<R>);
   const unsigned gs = (unsigned)g.vs * E;
-  const unsigned ns = (unsigned)g.vs * E;
-  const MrhsIn<R> in{make_rsrc(p ? hin.in_even : hin.in_odd, (size_t)12 * nr * ns), (unsigned)nr * ns, ns};
+  const auto in = make_mrhs_in<R>(p ? hin.in_even : hin.in_odd, g, nr);
+  const size_t ps = (size_t)nr * g.vs;
   int c[4] = {0, 0, 0, 0};
   int nf = 0, nb = 0;
   if (active) {
@@ -226,20 +313,22 @@ __global__ __launch_bounds__(256) void k_hop_mrhs(Geom g, int nr, int G, int nbp
         Ub.m[k] = ld_buf<R>(rub, (unsigned)nb * E, k * gs);
       }
     } else {
-#pragma unroll
-      for (int k = 0; k < 6; ++k) {
-        Uf.m[k] = ld_buf<R>(ruf, (unsigned)cb * E, k * gs);
-        Ub.m[k] = ld_buf<R>(rub, (unsigned)nb * E, k * gs);
-      }
+      load_two_rows<R, false>(ruf, (unsigned)cb * 16u, (unsigned)g.vs * 16u, Uf);
+      load_two_rows<R, false>(rub, (unsigned)nb * 16u, (unsigned)g.vs * 16u, Ub);
       third_row(Uf);
       third_row(Ub);
     }
   }
+  int buf = 0;
   for (int n = n0; n < n1; ++n) {
     if (!((act >> (n - n0)) & 1u)) continue;  // uniform: the block's mask
-    C<R> acc[12];
+    typename Epi::Pre pre{};
+    C<R> acc[12], sum[P::NC];
+    const size_t at = (size_t)n * g.vs + cb;
+    const bool owner = active && mu < P::kOwners;
 #pragma unroll
     for (int k = 0; k < 12; ++k) acc[k] = czero<R>();
+    if (owner) pre = epi.pre(p, ps, mu, at);
     if (active) {
       if (!kKeepLinks) {
 #pragma unroll
@@ -256,30 +345,31 @@ __global__ __launch_bounds__(256) void k_hop_mrhs(Geom g, int nr, int G, int nbp
         default: hop_dir_u<R, 3, DAG>(g, Uf, Ub, in, of, ob, c, acc); break;
       }
     }
-#pragma unroll
-    for (int k = 0; k < 12; ++k) {
-      R2<R> v;
-      v.x = acc[k].re;
-      v.y = acc[k].im;
-      lds[mu][k][lane] = v;
+    switch (mu) {
+      case 0: X::template share<0>(acc, lds[buf], lane, sum); break;
+      case 1: X::template share<1>(acc, lds[buf], lane, sum); break;
+      case 2: X::template share<2>(acc, lds[buf], lane, sum); break;
+      default: X::template share<3>(acc, lds[buf], lane, sum); break;
     }
     __syncthreads();
     double red = 0.0;
-    if (active) {
+    if (owner) {
 #pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        const int k = 3 * mu + i;
-        const R2<R> a = lds[0][k][lane], b = lds[1][k][lane], cc = lds[2][k][lane], d = lds[3][k][lane];
-        epi.apply(p, ((size_t)k * nr + n) * g.vs + cb, n,
-                  cmk<R>(((a.x + b.x) + cc.x) + d.x, ((a.y + b.y) + cc.y) + d.y), red);
+      for (int src = 0; src < 3; ++src) {
+        C<R> b[P::NC];
+        P::ld(X::strip(lds[buf], mu, src), 64, 0, lane, b);
+#pragma unroll
+        for (int q = 0; q < P::NC; ++q) sum[q] += b[q];
       }
+      epi.apply(p, ps, mu, at, n, sum, red, pre);
     }
     if constexpr (Epi::kReduce) {
       red = wave_sum(red);
       if (lane == 0) wred[mu][n - n0] = red;
     }
-    __syncthreads();
+    buf ^= 1;
   }
+  if constexpr (Epi::kReduce) __syncthreads();
   if constexpr (Epi::kReduce) {
     const int t = threadIdx.x;
     if (t < n1 - n0) {
@@ -383,9 +473,7 @@ __device__ __forceinline__ void mfma_hop(const MrhsIn<float>& in, unsigned osite
     const int nl = j + 4 * q;
     if ((live >> nl) & 1u) {
       C<float> psi[12];
-      const unsigned o = in.off(0, n0 + nl) + osite;
-#pragma unroll
-      for (int k = 0; k < 12; ++k) psi[k] = in.ld(o, k);
+      in.all(in.off(0, n0 + nl) + osite, psi);
       project<float, MU, S>(psi, h[q]);
     } else {
 #pragma unroll
@@ -430,9 +518,9 @@ __device__ __forceinline__ void mfma_dir(const Geom& g, const MrhsIn<float>& in,
   const BufRsrc ruf = make_rsrc(gptr<float>(gauge, g, p, MU), (size_t)9 * gs);
   const BufRsrc rub = make_rsrc(gptr<float>(gauge, g, 1 - p, MU), (size_t)9 * gs);
   const float bcs = (float)g.bc;
-  mfma_hop<MU, SF, false, G>(in, (unsigned)nf * E, ruf, (unsigned)cb * E, gs, j, n0, live,
+  mfma_hop<MU, SF, false, G>(in, (unsigned)nf * 16u, ruf, (unsigned)cb * E, gs, j, n0, live,
                              MU == 3 && c[3] == g.L[3] - 1, bcs, out);
-  mfma_hop<MU, -SF, true, G>(in, (unsigned)nb * E, rub, (unsigned)nb * E, gs, j, n0, live, MU == 3 && c[3] == 0,
+  mfma_hop<MU, -SF, true, G>(in, (unsigned)nb * 16u, rub, (unsigned)nb * E, gs, j, n0, live, MU == 3 && c[3] == 0,
                              bcs, out);
 }
 
@@ -461,9 +549,7 @@ __global__ __launch_bounds__(256) void k_hop_mrhs_mfma(Geom g, int nr, int nbp, 
   }
   __syncthreads();
   const unsigned act = s_act;
-  constexpr unsigned E = sizeof(float2);
-  const unsigned ns = (unsigned)g.vs * E;
-  const MrhsIn<float> in{make_rsrc(p ? hin.in_even : hin.in_odd, (size_t)12 * nr * ns), (unsigned)nr * ns, ns};
+  const auto in = make_mrhs_in<float>(p ? hin.in_even : hin.in_odd, g, nr);
   C<float> out[NL][12];
 #pragma unroll
   for (int q = 0; q < NL; ++q)
@@ -488,9 +574,9 @@ __global__ __launch_bounds__(256) void k_hop_mrhs_mfma(Geom g, int nr, int nbp, 
     for (int k = 0; k < 12; ++k) lds[mu][j + 4 * q][k][sb] = make_float2(out[q][k].re, out[q][k].im);
   __syncthreads();
   // epilogue: thread t owns right-hand side nl = t / (256 / G) of the group
-  // and components k = kq, kq + KS, ... of site t % 16
+  // and colours kq, kq + KS, ... of site t % 16
   constexpr int TPR = 256 / G;   // threads per right-hand side (32 or 64)
-  constexpr int KS = TPR / 16;   // component stride (2 or 4)
+  constexpr int KS = TPR / 16;   // colour stride (2 or 4)
   const int nl = threadIdx.x / TPR, q = threadIdx.x % TPR;
   const int site = q & 15, kq = q >> 4;
   const int ocb = blk * 16 + site;
@@ -498,12 +584,17 @@ __global__ __launch_bounds__(256) void k_hop_mrhs_mfma(Geom g, int nr, int nbp, 
   double red = 0.0;
   if (run) {
     const int n = n0 + nl;
+    const size_t ps = (size_t)nr * g.vs, at = (size_t)n * g.vs + ocb;
+    for (int own = kq; own < 3; own += KS) {
+      C<float> sum[4];
 #pragma unroll
-    for (int k = kq; k < 12; k += KS) {
-      const float2 a = lds[0][nl][k][site], b = lds[1][nl][k][site], cc = lds[2][nl][k][site],
-                   d = lds[3][nl][k][site];
-      epi.apply(p, ((size_t)k * nr + n) * g.vs + ocb, n, cmk<float>(((a.x + b.x) + cc.x) + d.x,
-                                                                     ((a.y + b.y) + cc.y) + d.y), red);
+      for (int j4 = 0; j4 < 4; ++j4) {
+        const int k = 3 * j4 + own;
+        const float2 a = lds[0][nl][k][site], b = lds[1][nl][k][site], cc = lds[2][nl][k][site],
+                     d = lds[3][nl][k][site];
+        sum[j4] = cmk<float>(((a.x + b.x) + cc.x) + d.x, ((a.y + b.y) + cc.y) + d.y);
+      }
+      epi.apply(p, ps, own, at, n, sum, red, epi.pre(p, ps, own, at));
     }
   }
   if constexpr (Epi::kReduce) {
@@ -580,9 +671,9 @@ hipError_t launch_mhop_schur_norm(const Geom& g, int nr, int G, HopIn<R> hin, R2
 }
 
 template <typename R, bool DAG>
-hipError_t launch_mhop_schur_cg(const Geom& g, int nr, int G, HopIn<R> hin, const R2<R>* w, R2<R>* x, R2<R>* r,
-                                const R2<R>* p, const double* coef, BatchState* st, Reduce red, hipStream_t s) {
-  MEpiSchurCG<R> e{w, x, r, p, coef, st};
+hipError_t launch_mhop_schur_cg(const Geom& g, int nr, int G, HopIn<R> hin, const R2<R>* w, R2<R>* r,
+                                const double* coef, BatchState* st, Reduce red, hipStream_t s) {
+  MEpiSchurCG<R> e{w, r, coef, st};
   hipError_t err = mlaunch<R, DAG>(g, nr, G, 1, hin, e, red, s);
   if (err != hipSuccess) return err;
   return launch_mfinalize(kFinCgStep, mrhs_nbp(g, G), nr, red, st, 0.0, 0, s);
@@ -612,8 +703,8 @@ hipError_t launch_mhop_residual(const Geom& g, int nr, int G, HopIn<double> hin,
                                                 BatchState*, const double*, Reduce, const double*);              \
   template hipError_t launch_mhop_schur_norm<R, DAG>(const Geom&, int, int, HopIn<R>, R2<R>*, const R2<R>*,      \
                                                       const double*, BatchState*, Reduce, hipStream_t);         \
-  template hipError_t launch_mhop_schur_cg<R, DAG>(const Geom&, int, int, HopIn<R>, const R2<R>*, R2<R>*, R2<R>*, \
-                                                    const R2<R>*, const double*, BatchState*, Reduce, hipStream_t);
+  template hipError_t launch_mhop_schur_cg<R, DAG>(const Geom&, int, int, HopIn<R>, const R2<R>*, R2<R>*,         \
+                                                    const double*, BatchState*, Reduce, hipStream_t);
 
 LGT_INST_MHOP(double, false)
 LGT_INST_MHOP(double, true)
@@ -626,10 +717,14 @@ template hipError_t launch_mhop_residual<true>(const Geom&, int, int, HopIn<doub
 
 // ---------------------------------------------------------------------------
 // Vector kernels over multi-RHS fields (padding included, except in sums):
-// grid (site blocks, 12 * nr slabs);
-// slab s of a half field holds component s / nr of right-hand side s % nr.
+// grid (site blocks, planes * nr slabs); slab s of a half field holds plane
+// s / nr of right-hand side s % nr.
 // ---------------------------------------------------------------------------
-static inline dim3 slab_grid(int vs, int nr) { return dim3((vs + 255) / 256, 12 * nr); }
+template <typename R> static inline dim3 plane_grid(int vs, int nr) {
+  return dim3((vs + 255) / 256, Planes<R, R2<R>>::kPlanes * nr);
+}
+// a thread takes the four spins of a colour (FP64 beside FP32 fields, see Planes)
+static inline dim3 colour_grid(int vs, int nr) { return dim3((vs + 255) / 256, 3 * nr); }
 
 // per-RHS |a|^2 over ncomp components (12: half field, 24: full field):
 // grid (nbx, nr), block (bx, n) sums its sites over all components into
@@ -664,7 +759,6 @@ hipError_t launch_mnorm(int vh, int vs, int ncomp, int nr, const R2<R>* a, Reduc
   return launch_mfinalize(kFinResult1, nb, nr, red, nullptr, 0.0, 0, s);
 }
 template hipError_t launch_mnorm<double>(int, int, int, int, const double2*, Reduce, hipStream_t);
-template hipError_t launch_mnorm<float>(int, int, int, int, const float2*, Reduce, hipStream_t);
 
 // After the finalize of an iteration: x += alpha_n p for every right-hand
 // side whose recursion ran it (still running, or stopped by this finalize:
@@ -683,26 +777,17 @@ __global__ __launch_bounds__(256) void k_mxpay(int vs, int nr, const R2<R>* __re
   if (!ran && !upd) return;
   const int s = blockIdx.x * 256 + threadIdx.x;
   if (s >= vs) return;
+  using V = R __attribute__((ext_vector_type(16 / sizeof(R))));
   const size_t i = (size_t)blockIdx.y * vs + s;
-  R2<R> pv = p[i];
-  if (ran) {
-    const R alpha = R(st->alpha[n]);
-    R2<R> xv = x[i];
-    xv.x += alpha * pv.x;
-    xv.y += alpha * pv.y;
-    x[i] = xv;
-  }
-  if (upd) {
-    const R beta = R(st->beta[n]);
-    const R2<R> rv = r[i];
-    pv.x = rv.x + beta * pv.x;
-    pv.y = rv.y + beta * pv.y;
-    p[i] = pv;
-  }
+  V* __restrict__ pp = reinterpret_cast<V*>(p) + i;
+  V* __restrict__ xp = reinterpret_cast<V*>(x) + i;
+  V pv = *pp;
+  if (ran) *xp += R(st->alpha[n]) * pv;
+  if (upd) *pp = reinterpret_cast<const V*>(r)[i] + R(st->beta[n]) * pv;
 }
 template <typename R>
 hipError_t launch_mxpay(int vs, int nr, const R2<R>* r, R2<R>* p, R2<R>* x, BatchState* st, hipStream_t s) {
-  hipLaunchKernelGGL((k_mxpay<R>), slab_grid(vs, nr), dim3(256), 0, s, vs, nr, r, p, x, st);
+  hipLaunchKernelGGL((k_mxpay<R>), plane_grid<R>(vs, nr), dim3(256), 0, s, vs, nr, r, p, x, st);
   return hipGetLastError();
 }
 template hipError_t launch_mxpay<double>(int, int, const double2*, double2*, double2*, BatchState*, hipStream_t);
@@ -713,17 +798,24 @@ __global__ __launch_bounds__(256) void k_mmixed_update(int vs, int nr, float2* x
                                                        const double* __restrict__ scale) {
   const int s = blockIdx.x * 256 + threadIdx.x;
   if (s >= vs) return;
-  const size_t i = (size_t)blockIdx.y * vs + s;
-  const double sc = scale[blockIdx.y % nr];
-  const float2 v = xs[i];
-  double2 xv = x[i];
-  xv.x += sc * (double)v.x;
-  xv.y += sc * (double)v.y;
-  x[i] = xv;
-  xs[i] = make_float2(0.f, 0.f);
+  const int own = blockIdx.y / nr, n = blockIdx.y % nr;
+  const size_t ps = (size_t)nr * vs, i = (size_t)n * vs + s;
+  const double sc = scale[n];
+  C<float> v[4];
+  C<double> xv[4];
+  Planes<float, float2>::ld(xs, ps, own, i, v);
+  ld_colour(x, ps, own, i, xv);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    xv[q].re += sc * (double)v[q].re;
+    xv[q].im += sc * (double)v[q].im;
+    v[q] = czero<float>();
+  }
+  st_colour(x, ps, own, i, xv);
+  Planes<float, float2>::st(xs, ps, own, i, v);
 }
 hipError_t launch_mmixed_update(int vs, int nr, float2* xs, double2* x, const double* scale, hipStream_t s) {
-  hipLaunchKernelGGL(k_mmixed_update, slab_grid(vs, nr), dim3(256), 0, s, vs, nr, xs, x, scale);
+  hipLaunchKernelGGL(k_mmixed_update, colour_grid(vs, nr), dim3(256), 0, s, vs, nr, xs, x, scale);
   return hipGetLastError();
 }
 
@@ -734,22 +826,25 @@ __global__ __launch_bounds__(256) void k_mrescale(int vs, int nr, const double2*
                                                   const double* __restrict__ pscale) {
   const int s = blockIdx.x * 256 + threadIdx.x;
   if (s >= vs) return;
-  const int n = blockIdx.y % nr;
-  const size_t i = (size_t)blockIdx.y * vs + s;
-  const double sg = sigma[n];
-  const double2 v = r64[i];
-  const float2 w = make_float2((float)(sg * v.x), (float)(sg * v.y));
-  r[i] = w;
-  if (restart[n]) {
-    p[i] = w;
-  } else {
-    const float2 q = p[i];
-    p[i] = make_float2((float)(pscale[n] * (double)q.x), (float)(pscale[n] * (double)q.y));
+  const int own = blockIdx.y / nr, n = blockIdx.y % nr;
+  const size_t ps = (size_t)nr * vs, i = (size_t)n * vs + s;
+  const double sg = sigma[n], sp = pscale[n];
+  C<double> v[4];
+  C<float> w[4], q[4];
+  ld_colour(r64, ps, own, i, v);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) w[k] = {(float)(sg * v[k].re), (float)(sg * v[k].im)};
+  Planes<float, float2>::st(r, ps, own, i, w);
+  if (!restart[n]) {
+    Planes<float, float2>::ld(p, ps, own, i, q);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = {(float)(sp * (double)q[k].re), (float)(sp * (double)q[k].im)};
   }
+  Planes<float, float2>::st(p, ps, own, i, w);
 }
 hipError_t launch_mrescale(int vs, int nr, const double2* r64, const double* sigma, float2* r, float2* p,
                            const int* restart, const double* pscale, hipStream_t s) {
-  hipLaunchKernelGGL(k_mrescale, slab_grid(vs, nr), dim3(256), 0, s, vs, nr, r64, sigma, r, p, restart, pscale);
+  hipLaunchKernelGGL(k_mrescale, colour_grid(vs, nr), dim3(256), 0, s, vs, nr, r64, sigma, r, p, restart, pscale);
   return hipGetLastError();
 }
 
@@ -871,7 +966,7 @@ hipError_t launch_mfinalize(int mode, int nblk, int nr, Reduce red, BatchState* 
   return hipGetLastError();
 }
 
-// element (k, n, site) of a multi-RHS field is at (k nr + n) vs + site
+// element (k, n, site) of a multi-RHS FP64 field is at (k nr + n) vs + site
 __global__ __launch_bounds__(256) void k_mzero_rhs(size_t tot, int vs, int nr, double2* __restrict__ f,
                                                    unsigned mask) {
   const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;

@@ -107,17 +107,11 @@ template <> struct Store<double, double2> {
   static __device__ __forceinline__ C<double> ld(const double2* p) { return lgt::ld<double>(p); }
   static __device__ __forceinline__ void st(double2* p, C<double> v) { lgt::st<double>(p, v); }
   static __device__ __forceinline__ C<double> round(C<double> v) { return v; }
-  static __device__ __forceinline__ C<double> ld_buf(BufRsrc r, unsigned vo, unsigned so) {
-    return lgt::ld_buf<double>(r, vo, so);
-  }
 };
 template <> struct Store<float, float2> {
   static __device__ __forceinline__ C<float> ld(const float2* p) { return lgt::ld<float>(p); }
   static __device__ __forceinline__ void st(float2* p, C<float> v) { lgt::st<float>(p, v); }
   static __device__ __forceinline__ C<float> round(C<float> v) { return v; }
-  static __device__ __forceinline__ C<float> ld_buf(BufRsrc r, unsigned vo, unsigned so) {
-    return lgt::ld_buf<float>(r, vo, so);
-  }
 };
 template <> struct Store<float, Bf16c> {
   static __device__ __forceinline__ C<float> unpack(unsigned w) {
@@ -130,10 +124,106 @@ template <> struct Store<float, Bf16c> {
   static __device__ __forceinline__ C<float> round(C<float> v) {
     return {bf16_to_f32(f32_to_bf16(v.re)), bf16_to_f32(f32_to_bf16(v.im))};
   }
-  static __device__ __forceinline__ C<float> ld_buf(BufRsrc r, unsigned vo, unsigned so) {
-    return unpack((unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, vo, so, 0));
+};
+
+// ---------------------------------------------------------------------------
+// How a half spinor field lies in memory: planes of one 16-byte vector a
+// site, whatever the storage type, so that every access of a lane is 16 bytes.
+//   FP64    12 planes, one component each: plane 3 spin + colour
+//   FP32     6 planes of two components: plane 2 colour + a holds spins 2a, 2a+1
+//   BF16     3 planes of four components: plane colour holds all four spins
+// A wave's load of 64 float2 costs the L1 the cycles of a load of 64 float4
+// (17.8 and 17.9 a wave load measured from the L1, 35.8 and 43.7 from the L2),
+// and the FP32 hops, with 36 such loads a lane, were bound there.  One plane a
+// component against these planes: FP32 hop 6.1 -> 5.5 us at 16^4, 32.1 -> 30.2
+// at 24^3x48 (there the last-level cache bounds it), 120 -> 107 at 32^3x64;
+// batched with 12 right-hand sides at 16^4 35 -> 28, with 4 at 24^3x48 131 ->
+// 101.
+// Owners: the epilogue of a hop gives wave `own` the components comp(own, q),
+// q < NC, of the block's sites -- a spin in FP64, a colour otherwise -- which
+// are whole planes.  ps: plane stride and i: place in a plane, in vectors.
+// ---------------------------------------------------------------------------
+typedef float v4f32 __attribute__((ext_vector_type(4)));
+typedef unsigned v4u32 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4u32 ld_buf16(BufRsrc r, unsigned voff, unsigned soff) {
+  return __builtin_bit_cast(v4u32, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+}
+__device__ __forceinline__ void halves(v4f32 v, C<float>& a, C<float>& b) {
+  a = {v.x, v.y};
+  b = {v.z, v.w};
+}
+
+template <typename R, typename T> struct Planes;
+template <> struct Planes<double, double2> {
+  static constexpr int kOwners = 4, NC = 3, kPlanes = 12;
+  static __device__ __forceinline__ constexpr int comp(int own, int q) { return 3 * own + q; }
+  static __device__ __forceinline__ void ld(const double2* f, size_t ps, int own, size_t i, C<double>* v) {
+#pragma unroll
+    for (int q = 0; q < NC; ++q) v[q] = lgt::ld<double>(f + (3 * own + q) * ps + i);
+  }
+  static __device__ __forceinline__ void st(double2* f, size_t ps, int own, size_t i, const C<double>* v) {
+#pragma unroll
+    for (int q = 0; q < NC; ++q) lgt::st<double>(f + (3 * own + q) * ps + i, v[q]);
+  }
+  // all twelve components at byte offset o of planes ks bytes apart
+  static __device__ __forceinline__ void all(BufRsrc rs, unsigned o, unsigned ks, C<double>* psi) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) psi[k] = ld_buf<double>(rs, o, k * ks);
   }
 };
+template <> struct Planes<float, float2> {
+  static constexpr int kOwners = 3, NC = 4, kPlanes = 6;
+  static __device__ __forceinline__ constexpr int comp(int own, int q) { return 3 * q + own; }
+  static __device__ __forceinline__ void ld(const float2* f, size_t ps, int own, size_t i, C<float>* v) {
+    const v4f32* p = reinterpret_cast<const v4f32*>(f) + 2 * own * ps + i;
+    halves(p[0], v[0], v[1]);
+    halves(p[ps], v[2], v[3]);
+  }
+  static __device__ __forceinline__ void st(float2* f, size_t ps, int own, size_t i, const C<float>* v) {
+    v4f32* p = reinterpret_cast<v4f32*>(f) + 2 * own * ps + i;
+    p[0] = v4f32{v[0].re, v[0].im, v[1].re, v[1].im};
+    p[ps] = v4f32{v[2].re, v[2].im, v[3].re, v[3].im};
+  }
+  static __device__ __forceinline__ void all(BufRsrc rs, unsigned o, unsigned ks, C<float>* psi) {
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      const int i = j >> 1, a = j & 1;
+      halves(__builtin_bit_cast(v4f32, ld_buf16(rs, o, j * ks)), psi[6 * a + i], psi[6 * a + 3 + i]);
+    }
+  }
+};
+template <> struct Planes<float, Bf16c> {
+  static constexpr int kOwners = 3, NC = 4, kPlanes = 3;
+  static __device__ __forceinline__ constexpr int comp(int own, int q) { return 3 * q + own; }
+  static __device__ __forceinline__ void ld(const Bf16c* f, size_t ps, int own, size_t i, C<float>* v) {
+    const v4u32 w = reinterpret_cast<const v4u32*>(f)[own * ps + i];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = Store<float, Bf16c>::unpack(w[q]);
+  }
+  static __device__ __forceinline__ void st(Bf16c* f, size_t ps, int own, size_t i, const C<float>* v) {
+    v4u32 w;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w[q] = f32_to_bf16(v[q].re) | (f32_to_bf16(v[q].im) << 16);
+    reinterpret_cast<v4u32*>(f)[own * ps + i] = w;
+  }
+  static __device__ __forceinline__ void all(BufRsrc rs, unsigned o, unsigned ks, C<float>* psi) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const v4u32 w = ld_buf16(rs, o, i * ks);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) psi[3 * q + i] = Store<float, Bf16c>::unpack(w[q]);
+    }
+  }
+};
+// FP64 components of a colour's four spins, as the FP32 owners take them
+__device__ __forceinline__ void ld_colour(const double2* f, size_t ps, int colour, size_t i, C<double>* v) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) v[q] = lgt::ld<double>(f + (3 * q + colour) * ps + i);
+}
+__device__ __forceinline__ void st_colour(double2* f, size_t ps, int colour, size_t i, const C<double>* v) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) lgt::st<double>(f + (3 * q + colour) * ps + i, v[q]);
+}
 
 // Non-temporal store: output streams that are not re-read by this kernel.
 template <typename R> __device__ __forceinline__ void st_nt(R2<R>* p, C<R> a) {

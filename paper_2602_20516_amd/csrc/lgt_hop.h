@@ -65,28 +65,27 @@ __device__ __forceinline__ void reconstruct(const C<R>* w, C<R>* acc) {
   reconstruct_s<R, MU>(w, R(S), acc);
 }
 
-// Input loaders: off(site, n) gives the per-lane byte offset of (site, rhs n)
-// once per neighbour, ld(off, k) spinor component k there (as C<R>).  All
-// loads go through buffer resources with 32-bit offsets, so a field must
-// stay below 4 GiB (the host checks 12 * vh * nr * 16 < 2^32).
-//
-// A plain stored field, element (k, site, n) at (k*vh + site)*nr + n.
+// Input loader: off(site) gives the per-lane byte offset of a site, once per
+// neighbour, all(off, psi) its twelve components.  All loads go through
+// buffer resources with 32-bit offsets, so a field must stay below 4 GiB (the
+// host checks 12 * vh * nr * 16 < 2^32).
 template <typename R, typename T>
 struct SpinorIn {
   BufRsrc rs;
-  unsigned ks;  // component stride in bytes
-  unsigned nr;
-  __device__ __forceinline__ unsigned off(int site, int n) const {
-    return ((unsigned)site * nr + (unsigned)n) * (unsigned)sizeof(T);
-  }
-  __device__ __forceinline__ C<R> ld(unsigned o, int k) const { return Store<R, T>::ld_buf(rs, o, k * ks); }
+  unsigned ks;  // plane stride in bytes
+  __device__ __forceinline__ unsigned off(int site) const { return (unsigned)site * 16u; }
+  __device__ __forceinline__ void all(unsigned o, C<R>* psi) const { Planes<R, T>::all(rs, o, ks, psi); }
 };
 
+template <typename R, typename T>
+__device__ __forceinline__ SpinorIn<R, T> make_spinor_in(const T* half, const Geom& g) {
+  const unsigned ks = (unsigned)g.vs * 16u;
+  return {make_rsrc(half, (size_t)Planes<R, T>::kPlanes * ks), ks};
+}
 // loader for the input parity of output parity p
 template <typename R, typename T>
-__device__ __forceinline__ SpinorIn<R, T> make_loader(const HopIn<R, T>& h, const Geom& g, int p, int nr) {
-  const unsigned ks = (unsigned)g.vs * (unsigned)nr * (unsigned)sizeof(T);
-  return SpinorIn<R, T>{make_rsrc(p ? h.in_even : h.in_odd, (size_t)12 * ks), ks, (unsigned)nr};
+__device__ __forceinline__ SpinorIn<R, T> make_loader(const HopIn<R, T>& h, const Geom& g, int p) {
+  return make_spinor_in<R, T>(p ? h.in_even : h.in_odd, g);
 }
 
 // a b and conj(a) b as one multiply and one FMA per component
@@ -147,10 +146,28 @@ __device__ __forceinline__ void apply_bc(const Geom& g, C<R>* w) {
 // also holds the spinors).
 constexpr size_t kLinkStreamBytes = (size_t)192 << 20;
 
+// The first two rows of an SU(3) link from a two-row field: six complex
+// planes in FP64, three planes of two complex numbers in FP32 (16 bytes a
+// lane either way); o: byte offset, the field's planes 16 vs bytes apart.
+template <typename R, bool NT>
+__device__ __forceinline__ void load_two_rows(BufRsrc r, unsigned o, unsigned ks, M3<R>& U) {
+  if constexpr (sizeof(R) == 8) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) U.m[k] = NT ? ld_buf_nt<R>(r, o, k * ks) : ld_buf<R>(r, o, k * ks);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const v4f32 v = __builtin_bit_cast(v4f32, NT ? __builtin_amdgcn_raw_buffer_load_b128(r, o, k * ks, 2)
+                                                   : __builtin_amdgcn_raw_buffer_load_b128(r, o, k * ks, 0));
+      halves(v, U.m[2 * k], U.m[2 * k + 1]);
+    }
+  }
+}
+
 // Link U_mu(x) of parity p at checkerboard site cb from a packed field of
-// nk complex components per link: all nine, or the first two rows of an
-// SU(3) matrix, whose third row is the conjugate cross product of the two
-// (one load per component through a buffer resource; uniform branch).
+// nk complex components per link: all nine, one a plane, or the first two
+// rows of an SU(3) matrix (load_two_rows), whose third row is the conjugate
+// cross product of the two (uniform branch).
 template <typename R>
 __device__ __forceinline__ M3<R> load_link(const R2<R>* __restrict__ gauge, int nk, const Geom& g, int p, int mu,
                                            int cb) {
@@ -174,30 +191,23 @@ __device__ __forceinline__ M3<R> load_link(const R2<R>* __restrict__ gauge, int 
       for (int k = 0; k < 9; ++k) U.m[k] = ld_buf<R>(ru, (unsigned)cb * E, k * gs);
     }
   } else {
-    if (stream) {
-#pragma unroll
-      for (int k = 0; k < 6; ++k) U.m[k] = ld_buf_nt<R>(ru, (unsigned)cb * E, k * gs);
-    } else {
-#pragma unroll
-      for (int k = 0; k < 6; ++k) U.m[k] = ld_buf<R>(ru, (unsigned)cb * E, k * gs);
-    }
+    const unsigned o = (unsigned)cb * 16u, ks = (unsigned)g.vs * 16u;
+    if (stream) load_two_rows<R, true>(ru, o, ks, U);
+    else load_two_rows<R, false>(ru, o, ks, U);
     third_row(U);
   }
   return U;
 }
 
 // The hop from x + mu (forward) or x - mu (backward) along MU for output
-// site (p, cb) with coordinates c, right-hand side n of the loader's field,
-// added to acc.
+// site (p, cb) with coordinates c, added to acc.
 template <typename R, int MU, bool DAG, typename L>
 __device__ __forceinline__ void hop_fwd(const Geom& g, const R2<R>* __restrict__ gauge, int nk, const L& in, int p,
-                                        int cb, const int c[4], C<R>* acc, int n) {
+                                        int cb, const int c[4], C<R>* acc) {
   constexpr int SF = DAG ? +1 : -1;  // forward projector 1 + SF gamma
   C<R> psi[12], h[6], w[6];
   // (1 + SF gamma) U_mu(x) psi(x + mu)
-  const unsigned of = in.off(cb_shift(g, c, MU, +1), n);
-#pragma unroll
-  for (int k = 0; k < 12; ++k) psi[k] = in.ld(of, k);
+  in.all(in.off(cb_shift(g, c, MU, +1)), psi);
   project<R, MU, SF>(psi, h);
   const M3<R> U = load_link<R>(gauge, nk, g, p, MU, cb);
   umul(U, h, w);
@@ -206,14 +216,12 @@ __device__ __forceinline__ void hop_fwd(const Geom& g, const R2<R>* __restrict__
 }
 template <typename R, int MU, bool DAG, typename L>
 __device__ __forceinline__ void hop_bwd(const Geom& g, const R2<R>* __restrict__ gauge, int nk, const L& in, int p,
-                                        const int c[4], C<R>* acc, int n) {
+                                        const int c[4], C<R>* acc) {
   constexpr int SB = DAG ? -1 : +1;  // backward projector 1 + SB gamma
   C<R> psi[12], h[6], w[6];
   // (1 + SB gamma) U_mu(x - mu)^dag psi(x - mu)
   const int nb = cb_shift(g, c, MU, -1);
-  const unsigned ob = in.off(nb, n);
-#pragma unroll
-  for (int k = 0; k < 12; ++k) psi[k] = in.ld(ob, k);
+  in.all(in.off(nb), psi);
   project<R, MU, SB>(psi, h);
   const M3<R> U = load_link<R>(gauge, nk, g, 1 - p, MU, nb);
   umul_dag(U, h, w);
@@ -221,12 +229,12 @@ __device__ __forceinline__ void hop_bwd(const Geom& g, const R2<R>* __restrict__
   reconstruct<R, MU, SB>(w, acc);
 }
 
-// Both hops along MU (forward first), right-hand side n.
+// Both hops along MU (forward first).
 template <typename R, int MU, bool DAG, typename L>
 __device__ __forceinline__ void hop_dir(const Geom& g, const R2<R>* __restrict__ gauge, int nk, const L& in, int p,
-                                        int cb, const int c[4], C<R>* acc, int n) {
-  hop_fwd<R, MU, DAG>(g, gauge, nk, in, p, cb, c, acc, n);
-  hop_bwd<R, MU, DAG>(g, gauge, nk, in, p, c, acc, n);
+                                        int cb, const int c[4], C<R>* acc) {
+  hop_fwd<R, MU, DAG>(g, gauge, nk, in, p, cb, c, acc);
+  hop_bwd<R, MU, DAG>(g, gauge, nk, in, p, c, acc);
 }
 
 // One of the two hops along MU, chosen per lane (bwd): the form of the
@@ -244,21 +252,18 @@ __device__ __forceinline__ void hop_one(const Geom& g, const R2<R>* __restrict__
   const R s = bwd ? R(-SF) : R(SF);
   const int nb = cb_shift(g, c, MU, bwd ? -1 : +1);
   C<R> psi[12], h[6], w[6];
-  const unsigned o = in.off(nb, 0);
-#pragma unroll
-  for (int k = 0; k < 12; ++k) psi[k] = in.ld(o, k);
+  in.all(in.off(nb), psi);
   project_s<R, MU>(psi, s, h);
   // U_mu(x) of parity p at cb, or U_mu(x - mu) of parity 1 - p at nb
   const unsigned gs = (unsigned)g.vs * E;
   const BufRsrc ru = make_rsrc(gauge, (size_t)8 * nk * gs);
-  const unsigned lo = ((unsigned)(((bwd ? 1 - p : p) * 4 + MU) * nk) * (unsigned)g.vs + (unsigned)(bwd ? nb : cb)) * E;
+  const unsigned lk = (unsigned)(((bwd ? 1 - p : p) * 4 + MU) * nk) * gs, ls = (unsigned)(bwd ? nb : cb);
   M3<R> U;
   if (nk == 9) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) U.m[k] = ld_buf<R>(ru, lo, k * gs);
+    for (int k = 0; k < 9; ++k) U.m[k] = ld_buf<R>(ru, lk + ls * E, k * gs);
   } else {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) U.m[k] = ld_buf<R>(ru, lo, k * gs);
+    load_two_rows<R, false>(ru, lk + ls * 16u, (unsigned)g.vs * 16u, U);
     third_row(U);
   }
   M3<R> A;  // U, or U^dag on the backward lanes
@@ -280,14 +285,12 @@ __device__ __forceinline__ void hop_dir_u(const Geom& g, const M3<R>& Uf, const 
   constexpr int SF = DAG ? +1 : -1;
   constexpr int SB = -SF;
   C<R> psi[12], h[6], w[6];
-#pragma unroll
-  for (int k = 0; k < 12; ++k) psi[k] = in.ld(of, k);
+  in.all(of, psi);
   project<R, MU, SF>(psi, h);
   umul(Uf, h, w);
   if (MU == 3 && c[3] == g.L[3] - 1) apply_bc(g, w);
   reconstruct<R, MU, SF>(w, acc);
-#pragma unroll
-  for (int k = 0; k < 12; ++k) psi[k] = in.ld(ob, k);
+  in.all(ob, psi);
   project<R, MU, SB>(psi, h);
   umul_dag(Ub, h, w);
   if (MU == 3 && c[3] == 0) apply_bc(g, w);

@@ -49,12 +49,13 @@ enum { kDoneRunning = 0, kDoneConverged = 1, kDoneMaxIter = 2, kDoneBreakdown = 
 // Output layout of the gauge-type kernels (forces, link update).
 enum Layout { kCanonical = 0, kPacked = 1 };
 
-// Arguments of a hop launch.  Half-fields are [12][vh] complex; a "full"
-// spinor is even half followed by odd half.  T is the storage type of the
-// input spinor (R2<R>, or Bf16c for BF16-stored spinors).
+// Arguments of a hop launch.  Half-fields are twelve complex numbers a site
+// in the planes of their storage type (see Planes); a "full" spinor is even
+// half followed by odd half.  T is the storage type of the input spinor
+// (R2<R>, or Bf16c for BF16-stored spinors).
 template <typename R, typename T = R2<R>>
 struct HopIn {
-  const R2<R>* gauge;  // packed links [2][4][nk][vh]
+  const R2<R>* gauge;  // packed links [2][4][nk][vs] (FP32 two-row links: three planes of two)
   const T* in_even;
   const T* in_odd;
   int nk = 9;          // 9: full links; 6: the first two rows of SU(3) links (the third
@@ -208,7 +209,7 @@ hipError_t launch_dslash_direct(const Geom& g, const double2* U, const double2* 
 // launch_rescale_residual); the new state and the mailbox post come from
 // block 0.  A skipped iteration only posts (and holds an update).
 template <typename R, typename T>
-hipError_t launch_cg_step(int n, const R2<R>* r, T* p, SolverState* st, Reduce red, int nblk, hipStream_t s,
+hipError_t launch_cg_step(int vs, const R2<R>* r, T* p, SolverState* st, Reduce red, int nblk, hipStream_t s,
                           R2<R>* x);
 template <typename R>
 hipError_t launch_cg_init(int n, const R2<R>* b, R2<R>* r, R2<R>* p, R2<R>* x, SolverState* st,
@@ -221,8 +222,11 @@ hipError_t launch_copy64(int n, const double2* x, double2* y, hipStream_t s);
 hipError_t launch_xmy64(int n, const double2* x, double2* y, hipStream_t s);             // y = x - y
 hipError_t launch_zero64(int n, double2* y, hipStream_t s);
 hipError_t launch_zero32(int n, float2* y, hipStream_t s);
-hipError_t launch_convert_64_32(int n, const double2* x, float2* y, hipStream_t s);
-// Links in two-row form: Uc[p][mu][6][vh] = rows 0 and 1 of U, and flag set
+hipError_t launch_convert_64_32(int n, const double2* x, float2* y, hipStream_t s);  // links: same planes
+// FP32 copy of nr half spinor fields in the batched layout (nr = 1: one half field), see Planes
+hipError_t launch_half_64_32(int vs, int nr, const double2* x, float2* y, hipStream_t s);
+// Links in two-row form: Uc[p][mu] = rows 0 and 1 of U in six complex planes
+// (FP64) or three planes of two (FP32), and flag set
 // to 1 (never cleared here) if for some link the third row stored in U is not
 // the conjugate cross product of the first two (FP32 to 1e-5, FP64 to 1e-14),
 // i.e. the links are not SU(3) and must not be compressed.
@@ -239,17 +243,17 @@ hipError_t launch_compress_links(const Geom& g, const double2* U64, double2* Uc,
 //     and nupd counted; a stop is posted to the mailbox
 //   launch_rescale_residual_dev: as launch_rescale_residual with sigma,
 //     restart and bscale from the state, and only if it is running
-hipError_t launch_mixed_fold(int n, float2* xs, double2* x, const SolverState* st, hipStream_t s);
+hipError_t launch_mixed_fold(int vs, float2* xs, double2* x, const SolverState* st, hipStream_t s);
 hipError_t launch_reliable_decide(int n, const double2* r64, Reduce red, SolverState* st, hipStream_t s);
 template <typename T>
-hipError_t launch_rescale_residual_dev(int n, const double2* r64, float2* r, T* p, const SolverState* st,
+hipError_t launch_rescale_residual_dev(int vs, const double2* r64, float2* r, T* p, const SolverState* st,
                                        hipStream_t s);
 // reliable update of the FP32 recursion: r = (float)(sigma r64); then the
 // next search direction p = r (restart) or p = r + bscale p (bscale = beta
 // of the stopping iteration times the change of units), p stored as T
 // (float2 or Bf16c)
 template <typename T>
-hipError_t launch_rescale_residual(int n, const double2* r64, double sigma, float2* r, T* p, int restart,
+hipError_t launch_rescale_residual(int vs, const double2* r64, double sigma, float2* r, T* p, int restart,
                                    double bscale, hipStream_t s);
 
 // Forces / gauge kernels (kernels_force.hip).  Gauge-type outputs: layout

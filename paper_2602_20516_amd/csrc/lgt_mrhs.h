@@ -28,7 +28,7 @@ hipError_t launch_mfinalize(int mode, int nblk, int nr, Reduce red, BatchState* 
 // rows of per-RHS partials a reducing batched hop writes (one per site block)
 int mrhs_hop_blocks(const Geom& g, int p_out);
 
-// Batched hops over nr fields in the [12][nr][vs] layout; G = right-hand
+// Batched hops over nr fields in the batched layout; G = right-hand
 // sides per block (1..nr; the links are loaded once per group of G) for the
 // VALU kernel, or G = -4 / -8 for the MFMA kernel (FP32 only) with groups
 // of 4 or 8 right-hand sides.
@@ -44,8 +44,8 @@ template <typename R, bool DAG>
 hipError_t launch_mhop_schur_norm(const Geom& g, int nr, int G, HopIn<R> hin, R2<R>* w, const R2<R>* x,
                                   const double* coef, BatchState* st, Reduce red, hipStream_t s);
 template <typename R, bool DAG>
-hipError_t launch_mhop_schur_cg(const Geom& g, int nr, int G, HopIn<R> hin, const R2<R>* w, R2<R>* x, R2<R>* r,
-                                const R2<R>* p, const double* coef, BatchState* st, Reduce red, hipStream_t s);
+hipError_t launch_mhop_schur_cg(const Geom& g, int nr, int G, HopIn<R> hin, const R2<R>* w, R2<R>* r,
+                                const double* coef, BatchState* st, Reduce red, hipStream_t s);
 // r = phi - (self + coef_n H in) over both parities, result[n] = |r_n|^2
 template <bool DAG>
 hipError_t launch_mhop_residual(const Geom& g, int nr, int G, HopIn<double> hin, const double2* self_full,

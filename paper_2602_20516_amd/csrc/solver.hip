@@ -129,7 +129,7 @@ constexpr int kFuseStepMaxVh = 65536;
 // and a separate step kernel.
 template <typename R, typename T, bool DAG>
 static void cg_iteration(const Geom& g, const R2<R>* gauge, double kappa, T* t, T* t2, T* w, R2<R>* x, R2<R>* r,
-                         T* p, SolverState* st, Reduce red, hipStream_t s, int n, bool fresh, int nk = 9) {
+                         T* p, SolverState* st, Reduce red, hipStream_t s, bool fresh, int nk = 9) {
   const double k2 = -kappa * kappa;
   constexpr bool kFused = std::is_same<T, R2<R>>::value;
   const bool fuse = kFused && g.vh <= kFuseStepMaxVh;
@@ -146,7 +146,7 @@ static void cg_iteration(const Geom& g, const R2<R>* gauge, double kappa, T* t, 
   // step kernel, which reads p anyway
   LGT_HIP((launch_hop_schur_cg<R, T, !DAG>(g, HopIn<R, T>{gauge, t2, t2, nk}, w, fuse ? x : nullptr, r, r, p, k2, st,
                                            red, s)));
-  if (!fuse) LGT_HIP((launch_cg_step<R, T>(n, r, p, st, red, hop_blocks(g, 1), s, x)));
+  if (!fuse) LGT_HIP((launch_cg_step<R, T>(g.vs, r, p, st, red, hop_blocks(g, 1), s, x)));
 }
 
 // CG on Mhat^dag Mhat z = rhs (odd half fields), FP64.  Returns the state's done code.
@@ -168,8 +168,8 @@ int lgt_ctx::cg_normal64(bool dag, double2* z, const double2* rhs, double tol, i
   bool fresh = true;
   for (int iter0 = 0;;) {
     drive(iter0, [&] {
-      if (dag) cg_iteration<double, double2, true>(g, links, kappa, t, t2, w, z, r, p, state, red(), stream, n, fresh, nk);
-      else cg_iteration<double, double2, false>(g, links, kappa, t, t2, w, z, r, p, state, red(), stream, n, fresh, nk);
+      if (dag) cg_iteration<double, double2, true>(g, links, kappa, t, t2, w, z, r, p, state, red(), stream, fresh, nk);
+      else cg_iteration<double, double2, false>(g, links, kappa, t, t2, w, z, r, p, state, red(), stream, fresh, nk);
       fresh = false;
     });
     LGT_HIP(hipMemcpyAsync(host_state, state, sizeof(SolverState), hipMemcpyDeviceToHost, stream));
@@ -231,7 +231,7 @@ int lgt_ctx::cg_normal_mixed(bool dag, double2* z, const double2* rhs, double to
   const double rr_target = tol * tol * bb;
   double sigma = 1.0 / std::sqrt(bb);
   LGT_HIP(launch_zero32(n, xs, stream));
-  LGT_HIP(launch_rescale_residual(n, rhs, sigma, rs, ps, 1, 0.0, stream));
+  LGT_HIP(launch_rescale_residual(vs, rhs, sigma, rs, ps, 1, 0.0, stream));
   SolverState s{};
   s.rr = 1.0;
   s.rr0 = 1.0;
@@ -253,8 +253,8 @@ int lgt_ctx::cg_normal_mixed(bool dag, double2* z, const double2* rhs, double to
   bool fresh = true;  // p has just been set: the next iteration's first hop is a plain t = H p
   for (;;) {
     const unsigned long long v = drive(iter0, [&] {
-      if (dag) cg_iteration<float, T, true>(g, links, kappa, ts, ts2, ws, xs, rs, ps, state, red(), stream, n, fresh, nk);
-      else cg_iteration<float, T, false>(g, links, kappa, ts, ts2, ws, xs, rs, ps, state, red(), stream, n, fresh, nk);
+      if (dag) cg_iteration<float, T, true>(g, links, kappa, ts, ts2, ws, xs, rs, ps, state, red(), stream, fresh, nk);
+      else cg_iteration<float, T, false>(g, links, kappa, ts, ts2, ws, xs, rs, ps, state, red(), stream, fresh, nk);
       fresh = false;
     }, min_epoch, false);
     unsigned act = (unsigned)(v >> 32);
@@ -272,17 +272,17 @@ int lgt_ctx::cg_normal_mixed(bool dag, double2* z, const double2* rhs, double to
     }
     const int code = (int)(act & 0xffu);
     if (code == kDoneUpdate || code == kDoneUpdateHeld || code == kDoneBreakdown) {
-      LGT_HIP(launch_mixed_fold(n, xs, z, state, stream));
+      LGT_HIP(launch_mixed_fold(vs, xs, z, state, stream));
       apply_mhat_dag_mhat64(dag, z, r64);          // r64 = A z
       LGT_HIP(launch_xmy64(n, rhs, r64, stream));  // r64 = rhs - A z
       LGT_HIP(launch_reliable_decide(n, r64, red(), state, stream));
-      LGT_HIP(launch_rescale_residual_dev<T>(n, r64, rs, ps, state, stream));
+      LGT_HIP(launch_rescale_residual_dev<T>(vs, r64, rs, ps, state, stream));
       min_epoch = (act >> 8) + 1;
       iter0 = dev_iter;
       fresh = true;
       continue;
     }
-    if (code == kDoneMaxIter) LGT_HIP(launch_mixed_fold(n, xs, z, state, stream));
+    if (code == kDoneMaxIter) LGT_HIP(launch_mixed_fold(vs, xs, z, state, stream));
     LGT_HIP(hipMemcpyAsync(host_state, state, sizeof(SolverState), hipMemcpyDeviceToHost, stream));
     sync();
     s = *host_state;
