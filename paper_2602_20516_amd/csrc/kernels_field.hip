@@ -273,10 +273,12 @@ template <> struct StepElem<float, Bf16c> {
   }
 };
 
+constexpr int kStepThreads = 512;
+
 template <typename R, typename T>
-__global__ __launch_bounds__(256) void k_cg_step(int n, int vs, int nblk, const double* __restrict__ partials,
-                                                 const R2<R>* __restrict__ r, T* __restrict__ p, SolverState* st,
-                                                 Mailbox* mb, R2<R>* __restrict__ x) {
+__global__ __launch_bounds__(kStepThreads) void k_cg_step(int n, int vs, int nblk, const double* __restrict__ partials,
+                                                          const R2<R>* __restrict__ r, T* __restrict__ p,
+                                                          SolverState* st, Mailbox* mb, R2<R>* __restrict__ x) {
   const int done0 = st->done;
   if (done0 != kDoneRunning) {  // the iteration was skipped (or block 0 below already stopped it)
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -291,7 +293,7 @@ __global__ __launch_bounds__(256) void k_cg_step(int n, int vs, int nblk, const 
   // block 0's writes below do not touch
   __shared__ double s_rr;
   double tot[1];
-  sum_partials<256, 1>(partials, nblk, tot);
+  sum_partials<kStepThreads, 1>(partials, nblk, tot);
   if (threadIdx.x == 0) s_rr = tot[0];
   __syncthreads();
   const double rr = s_rr;
@@ -305,33 +307,23 @@ __global__ __launch_bounds__(256) void k_cg_step(int n, int vs, int nblk, const 
   else if (iter >= st->max_iter) code = kDoneMaxIter;
   {
     // x += alpha p (this iteration's step, taken whatever the decision), then
-    // p = r + beta p unless the recursion stops; kTrip elements per thread and
-    // trip, all loads issued before the stores
+    // p = r + beta p unless the recursion stops
     using E = StepElem<R, T>;
-    constexpr int kTrip = E::W == 4 ? 2 : 4;
     const R b = R(beta), a = R(st->alpha);
     const bool upd = code == kDoneRunning;
-    const int stride = gridDim.x * 256, ne = n / E::W;
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < ne; i += kTrip * stride) {
-      C<R> rv[kTrip][E::W], pv[kTrip][E::W], xv[kTrip][E::W];
+    const int stride = gridDim.x * kStepThreads, ne = n / E::W;
+    for (int i = blockIdx.x * kStepThreads + threadIdx.x; i < ne; i += stride) {
+      C<R> rv[E::W], pv[E::W], xv[E::W];
+      E::ld_p(p, i, pv);
+      E::ld_x(x, i, vs, xv);
+      if (upd) E::ld_x(r, i, vs, rv);
 #pragma unroll
-      for (int j = 0; j < kTrip; ++j) {
-        if (i + j * stride >= ne) continue;
-        E::ld_p(p, i + j * stride, pv[j]);
-        E::ld_x(x, i + j * stride, vs, xv[j]);
-        if (upd) E::ld_x(r, i + j * stride, vs, rv[j]);
+      for (int q = 0; q < E::W; ++q) {
+        xv[q] += a * pv[q];
+        if (upd) pv[q] = C<R>{rv[q].re + b * pv[q].re, rv[q].im + b * pv[q].im};
       }
-#pragma unroll
-      for (int j = 0; j < kTrip; ++j) {
-        if (i + j * stride >= ne) continue;
-#pragma unroll
-        for (int q = 0; q < E::W; ++q) {
-          xv[j][q] += a * pv[j][q];
-          pv[j][q] = C<R>{rv[j][q].re + b * pv[j][q].re, rv[j][q].im + b * pv[j][q].im};
-        }
-        E::st_x(x, i + j * stride, vs, xv[j]);
-        if (upd) E::st_p(p, i + j * stride, pv[j]);
-      }
+      E::st_x(x, i, vs, xv);
+      if (upd) E::st_p(p, i, pv);
     }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -349,15 +341,14 @@ hipError_t launch_cg_step(int vs, const R2<R>* r, T* p, SolverState* st, Reduce 
                           R2<R>* x) {
   const int n = 12 * vs;
   if (nblk > red.capacity) return hipErrorInvalidValue;
-  // each block also sums the nblk partials (a few thousand on large
-  // lattices).  With 8-byte elements (FP32, BF16 pairs) a grid of about four
-  // elements per thread, at most 1024 blocks, keeps those re-reads small next
-  // to the vector work (16^4: 4.6 -> 4.1 us, 24^3x48: 23.2 -> 20.3 us); FP64
-  // elements keep enough loads in flight with one per thread (at most 2048
-  // blocks), which is faster for them at 16^4 (6.3 against 7.1 us).
-  const int nb = sizeof(R) == 4 ? std::max(1, std::min((n + 1023) / 1024, 1024))
-                                : std::max(1, std::min((n + 255) / 256, 2048));
-  hipLaunchKernelGGL((k_cg_step<R, T>), dim3(nb), dim3(256), 0, s, n, vs, nblk, red.partials, r, p, st, red.mbox, x);
+  // Bound by HBM and the memory-side cache; but each block also sums the nblk
+  // partials, one for 64 sites: at 32^3x64 128 KB a block, so blocks beyond
+  // one a CU cost more than they hide.  256 blocks of 512 threads (8 waves a
+  // CU) against 1024 or 2048 of 256 threads that took two or four elements a
+  // trip: FP32 at 32^3x64 104.6 -> 74.5 us, BF16 at 24^3x48 25.3 -> 20.9,
+  // FP64 at 24^3x48 52.2 -> 48.9 and at 32^3x64 182.9 -> 163.5.
+  const int nb = std::max(1, std::min((n / StepElem<R, T>::W + kStepThreads - 1) / kStepThreads, 256));
+  hipLaunchKernelGGL((k_cg_step<R, T>), dim3(nb), dim3(kStepThreads), 0, s, n, vs, nblk, red.partials, r, p, st, red.mbox, x);
   return hipGetLastError();
 }
 template hipError_t launch_cg_step<double, double2>(int, const double2*, double2*, SolverState*, Reduce, int,

@@ -250,7 +250,7 @@ struct EpiShiftResidual {
 template <typename R, typename T>
 struct EpiSchurNorm {  // w = x + coef * acc (odd sites), block partials of |w|^2 (of w as stored)
   static constexpr bool kReduce = true;
-  static constexpr bool kPrefetch = !std::is_same<T, Bf16c>::value;
+  static constexpr bool kPrefetch = true;
   T* w;
   const T* x;
   R coef;
@@ -426,9 +426,10 @@ __global__ __launch_bounds__(256) void k_hop(Geom g, int nbp, int p_fixed, In hi
   // 64-site blocks: the lane's epilogue operands at its own (site, spin =
   // wave) are independent of the hop, so they are loaded before it and
   // arrive while the neighbour loads are in flight (16^4 mixed force call
-  // 5.40 -> 5.15 ms, FP64 at 24^3x48 187 -> 183 ms).  Not for BF16-stored
-  // vectors, where holding them across the hop cost more than it saved
-  // (24^3x48: 65.0 -> 67.5 ms).
+  // 5.40 -> 5.15 ms, FP64 at 24^3x48 187 -> 183 ms).  With BF16-stored
+  // vectors only where there is one operand: three waves own the
+  // components, and holding x, r, p of a third of them across the hop costs
+  // registers (24^3x48: EpiSchurCG 31.8 -> 35.9 us, EpiSchurNorm 28.8 -> 27.9).
   typename Epi::Pre pre{};
   if constexpr (NS == 64 && Epi::kPrefetch) {
     if (active && mu < P::kOwners) pre = epi.pre(p, cb, mu);

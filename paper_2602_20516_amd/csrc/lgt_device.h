@@ -508,6 +508,7 @@ __device__ __forceinline__ void sum_partials(const double* partials, int nblk, d
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     double s = 0.0;
+#pragma unroll 8
     for (int i = threadIdx.x; i < nblk; i += NT) s += partials[(size_t)i * NV + k];
     out[k] = block_sum<NT>(s, sh);
   }
