@@ -383,6 +383,14 @@ struct EpiResidual {  // r = phi - (self + coef * acc) over both parities, block
 // group covers slice j % tgrp, chunk j / tgrp of that slice, so the t-hops
 // of a chunk are a few blocks apart and its z-hops 8 tgrp blocks apart.  A
 // bijection of the blocks of a parity: every site is still covered once.
+//
+// Hops onto odd sites take each XCD's blocks last first.  Hops alternate in
+// parity, so a hop starts where the one before it ended, and finds the links
+// and spinors of that end in the memory-side cache, which a hop of a large
+// lattice has streamed through (FP64 solve at 32^3x64: |w|^2 hop 303 -> 281
+// us, CG hop 332 -> 308; FP32 at 16^3x64 15.9 -> 14.4 and 16.9 -> 15.7; BF16
+// at 24^3x48 27.9 -> 26.6 and 31.8 -> 30.4; mixed FP32 force at 16^4 5.81 ->
+// 5.28 ms, where the XCD's own L2 holds part of that end).
 // ---------------------------------------------------------------------------
 // A wave's partial hops in its part of the LDS, in the planes of a half field
 // of 64 sites, and an owner's part of them back.
@@ -409,7 +417,7 @@ __global__ __launch_bounds__(256) void k_hop(Geom g, int nbp, int p_fixed, In hi
   if (epi.skip()) return;
   using P = typename Epi::P;
   __shared__ R2<R> lds[4][12][64];
-  const int lb = xcd_block(blockIdx.x, gridDim.x);
+  const int lb = xcd_block(blockIdx.x, gridDim.x, p_fixed == 1);
   const int p = p_fixed >= 0 ? p_fixed : lb / nbp;
   int blk = p_fixed >= 0 ? lb : lb % nbp;
   if (NS == 64 && tgrp > 0) {

@@ -458,9 +458,10 @@ template <typename R> __device__ __forceinline__ void store_m3(R2<R>* f, int vh,
 // blocks keeps each stencil's neighbours in that XCD's L2.
 // ---------------------------------------------------------------------------
 constexpr int kXcd = 8;
-__device__ __forceinline__ int xcd_block(int b, int nb) {
+__device__ __forceinline__ int xcd_block(int b, int nb, bool reverse = false) {
   int q = nb / kXcd, r = nb % kXcd;
   int x = b % kXcd, slot = b / kXcd;
+  if (reverse) slot = q - (x < r ? 0 : 1) - slot;  // the XCD's range, last block first
   return x < r ? x * (q + 1) + slot : r * (q + 1) + (x - r) * q + slot;
 }
 
