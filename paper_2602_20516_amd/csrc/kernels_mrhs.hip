@@ -219,13 +219,6 @@ __device__ __forceinline__ MrhsIn<R> make_mrhs_in(const R2<R>* half, const Geom&
   return {make_rsrc(half, (size_t)Planes<R, R2<R>>::kPlanes * ks), ks, ns};
 }
 
-// wave-level sum in a fixed butterfly order (all 64 lanes get the total)
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 // The partial hops of wave MU for the other owners: strip [owner][source] of
 // the exchange, the source counted without the owner's own wave, which keeps
 // its part in registers.

@@ -474,10 +474,35 @@ __device__ __forceinline__ int xcd_block(int b, int nb, bool reverse = false) {
 // executes an atomic or a device-scope fence, and every run gives the same
 // bits.
 // ---------------------------------------------------------------------------
+// Sum over the wave's 64 lanes (all active), in every lane.  Moves between
+// lanes in the vector ALU (rows of 16 first, then row to row): a shuffle's
+// exchange through the LDS unit costs a round trip for each of the six
+// steps, at the end of every reducing launch (FP64 hops at 12^4: |w|^2 6.5
+// -> 5.8 us, CG hop 7.2 -> 6.7, step hop 7.1 -> 6.7; FP32 at 16^4 6.1 -> 5.6,
+// 6.8 -> 6.3, 7.1 -> 6.6).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_step(double v) {
+  const uint2 u = __builtin_bit_cast(uint2, v);
+  uint2 m;
+  m.x = __builtin_amdgcn_update_dpp(0, (int)u.x, CTRL, ROWS, 0xf, true);
+  m.y = __builtin_amdgcn_update_dpp(0, (int)u.y, CTRL, ROWS, 0xf, true);
+  return v + __builtin_bit_cast(double, m);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = dpp_step<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8: lane 15 of a row holds its sum
+  v = dpp_step<0x112, 0xf>(v);
+  v = dpp_step<0x114, 0xf>(v);
+  v = dpp_step<0x118, 0xf>(v);
+  v = dpp_step<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+  v = dpp_step<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+  uint2 u = __builtin_bit_cast(uint2, v);
+  u.x = __builtin_amdgcn_readlane((int)u.x, 63);
+  u.y = __builtin_amdgcn_readlane((int)u.y, 63);
+  return __builtin_bit_cast(double, u);
+}
 template <int NT>
 __device__ __forceinline__ double block_sum(double v, double* sh) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  v = wave_sum(v);
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   __syncthreads();
   if (lane == 0) sh[w] = v;
