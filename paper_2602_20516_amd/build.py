@@ -19,7 +19,8 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblgt.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 
-SOURCES = ["kernels_hop.hip", "kernels_dslash.hip", "kernels_field.hip", "kernels_force.hip", "kernels_stout.hip",
+SOURCES = ["kernels_hop.hip", "kernels_hop_pair.hip", "kernels_dslash.hip", "kernels_field.hip",
+           "kernels_force.hip", "kernels_stout.hip",
            "kernels_mrhs.hip", "solver.hip", "smear.hip", "batch.hip", "multishift.hip", "noalloc.hip", "abi.hip"]
 
 ARCH = "gfx950"

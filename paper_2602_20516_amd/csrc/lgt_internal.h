@@ -110,6 +110,14 @@ int hop_blocks(const Geom& g, int p_out);
 // Lattices with at most this many sites per parity run the hop with 32
 // sites per block (half-wave hops), larger ones with 64.
 constexpr int kHopHalfWaveMaxVh = 8192;
+// Lattices with at most this many sites per parity run the CG iteration of
+// the FP32 and FP64 recursions as two launches of two hops each.  One box of
+// eight sites a CU is 2048; an FP64 box leaves no registers for a second one
+// on its CU, FP32 boxes fit twice but then share the vector units.  Solve to
+// 1e-11, four launches -> two: FP64 4^4 1740 -> 1386 us, 6^4 2271 -> 1798,
+// 8^4 2675 -> 2480, 8^3x10 2871 -> 4215; FP32 4^4 1961 -> 1449, 8^4 2801 ->
+// 2150, 8^3x12 3240 -> 2961, 8^3x16 3487 -> 3564.
+constexpr int kHopPairMaxVh32 = 3072, kHopPairMaxVh64 = 2048;
 // Above this many sites per parity the 64-site hop takes its blocks
 // t-fastest (when a t-slice holds a whole number of blocks).
 constexpr int kHopTOrderMinVh = 131072;
@@ -157,6 +165,19 @@ hipError_t launch_hop_axpy(const Geom& g, int p_out, HopIn<R, T> hin, T* out_eve
 template <typename R, bool DAG>
 hipError_t launch_hop_step(const Geom& g, const R2<R>* gauge, int nk, R2<R>* t, R2<R>* p, const R2<R>* r,
                            SolverState* st, Reduce red, hipStream_t s);
+// Hops (1) and (2), or (3) and (4), of a CG iteration in one launch
+// (kernels_hop_pair.hip), with the step of the previous iteration in the
+// first (not in a fresh iteration) and alpha in the second.  t_old: H p of
+// the previous iteration, t_new: of this one (another field; fresh: t_old is
+// not read).  hop_pair_used: the rule; elem: bytes of an R2<R>.
+bool hop_pair_used(const Geom& g, size_t elem);
+template <typename R, bool DAG>
+hipError_t launch_hop_pair_first(const Geom& g, const R2<R>* gauge, int nk, bool fresh, const R2<R>* t_old,
+                                 R2<R>* t_new, R2<R>* w, R2<R>* p, const R2<R>* r, double k2, SolverState* st,
+                                 Reduce red, hipStream_t s);
+template <typename R, bool DAG>
+hipError_t launch_hop_pair_second(const Geom& g, const R2<R>* gauge, int nk, const R2<R>* w, R2<R>* x, R2<R>* r,
+                                  const R2<R>* p, double k2, SolverState* st, Reduce red, hipStream_t s);
 // One CG iteration on Mhat^dag Mhat (Mhat = 1 - kappa^2 H_oe H_eo, odd sites)
 // is four hop launches and the step kernel:
 //  (1) t = H p                                      launch_hop_axpy (guard)
@@ -167,7 +188,7 @@ hipError_t launch_hop_step(const Geom& g, const R2<R>* gauge, int nk, R2<R>* t, 
 //  (5) rr, beta and the stop decision (every block sums the partials),
 //      x += alpha p, p = r + beta p unless stopping, block 0 records the
 //      state and posts                              launch_cg_step
-// (on small lattices (1) also does (5) of the previous iteration, see
+// (up to 2^16 sites a parity (1) also does (5) of the previous iteration, see
 // launch_hop_step, and (4) then takes the x update)
 // (for the dagger operator the roles of H and H^dag swap).  t, w, p are
 // stored as T; x and r as R2<R>.

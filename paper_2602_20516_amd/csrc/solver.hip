@@ -25,6 +25,7 @@
 #include <cmath>
 #include <cstring>
 #include <type_traits>
+#include <utility>
 
 #include "lgt_ctx.h"
 
@@ -126,12 +127,21 @@ constexpr int kFuseStepMaxVh = 65536;
 // solve and the first after a reliable update, where p has just been set):
 // there the first hop is a plain t = H p.  t keeps H p for the next
 // iteration's step, so the third hop writes t2.  Otherwise: the four hops
-// and a separate step kernel.
+// and a separate step kernel.  On the smallest lattices two launches do the
+// same as the four (see hop_pair_used).
 template <typename R, typename T, bool DAG>
-static void cg_iteration(const Geom& g, const R2<R>* gauge, double kappa, T* t, T* t2, T* w, R2<R>* x, R2<R>* r,
+static void cg_iteration(const Geom& g, const R2<R>* gauge, double kappa, T*& t, T*& t2, T* w, R2<R>* x, R2<R>* r,
                          T* p, SolverState* st, Reduce red, hipStream_t s, bool fresh, int nk = 9) {
   const double k2 = -kappa * kappa;
   constexpr bool kFused = std::is_same<T, R2<R>>::value;
+  if constexpr (kFused) {
+    if (hop_pair_used(g, sizeof(R2<R>))) {  // two launches; H p alternates between t and t2
+      LGT_HIP((launch_hop_pair_first<R, DAG>(g, gauge, nk, fresh, t, t2, w, p, r, k2, st, red, s)));
+      LGT_HIP((launch_hop_pair_second<R, !DAG>(g, gauge, nk, w, x, r, p, k2, st, red, s)));
+      std::swap(t, t2);
+      return;
+    }
+  }
   const bool fuse = kFused && g.vh <= kFuseStepMaxVh;
   if (fuse && !fresh) {
     if constexpr (kFused) LGT_HIP((launch_hop_step<R, DAG>(g, gauge, nk, t, p, r, st, red, s)));
