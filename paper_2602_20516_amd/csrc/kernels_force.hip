@@ -309,47 +309,36 @@ hipError_t launch_bilinear_sum(const Geom& g, const double2* U, const BilinearSu
 //                      + U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu) ],
 // so G = -(beta/3) A^dag and F = (beta/6) P[U A].
 // ---------------------------------------------------------------------------
-// The staple force in site-block form (see k_bilinear_sb): each thread sums
-// the six staples of its link one at a time, each as two 3x3 products, so
-// at most the running sum, one partial product and two links are live.
+// The staple force in site-block form (see k_bilinear_sb).  Bound by what the
+// L2 returns to the CU (links come from it at some 20 bytes a clock and CU;
+// 11 to 16 TB/s here, a multiple of what the memory has to deliver): a
+// thread reads 19 links, of which the four waves of the block share U_nu(x)
+// and U_nu(x-nu), the last factors of its staples.  Each of these is loaded
+// once and exchanged through LDS, 14 loads a thread (32^3x64: 1690 -> 1550
+// us, 16^4: 48.2 -> 44.4).  With U_nu(x) alone 1558 and 45.6; three waves a
+// SIMD instead of two, by fewer registers, 1684.  The stout levels, whose
+// exponential needs the registers, lose by the exchange (one level forward at
+// 24^3x48: 480 -> 560 us) and sum their staples thread by thread.
 template <int LAYOUT>
 __global__ __launch_bounds__(256) void k_gauge_force_sb(Geom g, const double2* __restrict__ U, double beta,
                                                         int mode, double dt, double2* out, BlockOrder order) {
-  __shared__ double2 sh[LAYOUT == kCanonical ? kSB : 1][36];
+  // the shared links; for the canonical layout then the [64][36] output staging
+  __shared__ StapleLinks links;
   __shared__ int sh_site[kSB];
   const int lb = xcd_block(blockIdx.x, gridDim.x);
   const int p = lb & 1, blk = gauge_site_block(lb, order, g.L[2]);
-  const int lane = threadIdx.x & 63, mu = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, mu = wave_id();
   const int cb = blk * kSB + lane;
   const bool active = cb < g.vh;
   int c[4];
   cb_coords(g, p, active ? cb : 0, c);
-  int xpm[4];
-  shifted(g, c, mu, +1, xpm);
-  M3<double> A;
-#pragma unroll
-  for (int k = 0; k < 9; ++k) A.m[k] = czero<double>();
-#pragma unroll
-  for (int k = 1; k < 4; ++k) {
-    const int nu = (mu + k) & 3;
-    int xpn[4], xmn[4], xpmmn[4];
-    shifted(g, c, nu, +1, xpn);
-    shifted(g, c, nu, -1, xmn);
-    shifted(g, xpm, nu, -1, xpmmn);
-    // U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-    M3<double> t = mmul_nd(link_at(U, g, xpm, nu), link_at(U, g, xpn, mu));
-    A = mmac_nd(A, t, link_at(U, g, c, nu));
-    // U_nu(x+mu-nu)^dag U_mu(x-nu)^dag U_nu(x-nu) = (U_mu(x-nu) U_nu(x+mu-nu))^dag U_nu(x-nu)
-    t = mmul(link_at(U, g, xmn, mu), link_at(U, g, xpmmn, nu));
-    A = mmac_dn(A, t, link_at(U, g, xmn, nu));
-  }
+  const M3<double> A = staple_block(U, g, p, active ? cb : 0, c, mu, lane, links);
   M3<double> M;
-  if (mode == 1) {
-    M = mscale(-beta / 3.0, mdag(A));
-  } else {
-    const M3<double> Ux = load_m3<double>(gptr<double>(U, g, p, mu), g.vs, active ? cb : 0);
-    M = mscale(beta / 6.0, proj_ta(mmul(Ux, A)));
-  }
+  if (mode == 1) M = mscale(-beta / 3.0, mdag(A));
+  else M = mscale(beta / 6.0, proj_ta(mmul(lds_link(links.own[mu], lane), A)));
+  double2 (*sh)[36] = reinterpret_cast<double2 (*)[36]>(&links);
+  static_assert(sizeof(StapleLinks) >= sizeof(double2) * kSB * 36, "the staging reuses the links' LDS");
+  if (LAYOUT == kCanonical) __syncthreads();  // every wave is done with the links
   emit_block<LAYOUT>(g, out, p, blk, lane, mu, mode, dt, M, active, lex_of(g, c), sh, sh_site);
 }
 

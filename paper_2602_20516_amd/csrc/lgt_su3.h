@@ -161,6 +161,43 @@ __device__ __forceinline__ M3<double> staple_A(const double2* U, const Geom& g, 
   return A;
 }
 
+// The same by a block of 256 threads, wave mu at the sites cb (of parity p,
+// coordinates c) of its 64 lanes, with the links that several of the waves
+// read, U_mu(x) and U_mu(x-mu), exchanged through LDS.
+struct StapleLinks {
+  double2 own[4][9][64], low[4][9][64];
+};
+__device__ __forceinline__ void lds_put(double2 (*s)[64], int lane, const M3<double>& u) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k) st<double>(&s[k][lane], u.m[k]);
+}
+__device__ __forceinline__ M3<double> lds_link(const double2 (*s)[64], int lane) {
+  M3<double> u;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) u.m[k] = ld<double>(&s[k][lane]);
+  return u;
+}
+__device__ __forceinline__ M3<double> staple_block(const double2* U, const Geom& g, int p, int cb, const int c[4],
+                                                   int mu, int lane, StapleLinks& s) {
+  lds_put(s.own[mu], lane, link_uni(U, g, p, mu, cb));
+  lds_put(s.low[mu], lane, link_uni(U, g, 1 - p, mu, cb_shift(g, c, mu, -1)));
+  __syncthreads();
+  int xpm[4];
+  shifted(g, c, mu, +1, xpm);
+  const int cpm = cb_of(g, xpm);
+  M3<double> A = mzero();
+#pragma unroll
+  for (int k = 1; k < 4; ++k) {
+    const int nu = (mu + k) & 3;
+    const int xpn = cb_shift(g, c, nu, +1), xmn = cb_shift(g, c, nu, -1), xpmmn = cb_shift(g, xpm, nu, -1);
+    M3<double> t = mmul_nd(link_uni(U, g, 1 - p, nu, cpm), link_uni(U, g, 1 - p, mu, xpn));
+    A = mmac_nd(A, t, lds_link(s.own[nu], lane));
+    t = mmul(link_uni(U, g, 1 - p, mu, xmn), link_uni(U, g, p, nu, xpmmn));
+    A = mmac_dn(A, t, lds_link(s.low[nu], lane));
+  }
+  return A;
+}
+
 // ---------------------------------------------------------------------------
 // exp(X) for traceless anti-Hermitian X, by Cayley-Hamilton: with Q = -iX
 // (Hermitian, traceless), exp(iQ) = f0 + f1 Q + f2 Q^2 and the f_j of
