@@ -521,10 +521,10 @@ hipError_t launch_mixed_fold(int vs, float2* xs, double2* x, const SolverState* 
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_reliable_decide(int nblk, const double* __restrict__ partials,
-                                                         SolverState* st, Mailbox* mb) {
-  double tot[2];
-  sum_partials<256, 2>(partials, nblk, tot);
+__global__ __launch_bounds__(1024) void k_reliable_decide(int nblk, const double* __restrict__ partials,
+                                                          SolverState* st, Mailbox* mb) {
+  double tot[1];
+  sum_partials<1024, 1>(partials, nblk, tot);
   if (threadIdx.x != 0) return;
   const double rr64 = tot[0];
   const int entry = st->done;
@@ -548,13 +548,9 @@ __global__ __launch_bounds__(256) void k_reliable_decide(int nblk, const double*
   st->done = code;
   post_progress(mb, st->iter, code != kDoneRunning ? action_word(st->epoch, code) : 0u);
 }
-hipError_t launch_reliable_decide(int n, const double2* r64, Reduce red, SolverState* st, hipStream_t s) {
-  const int nb = vec_blocks(n);
-  if (nb > red.capacity) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_norm_dot, dim3(nb), dim3(256), 0, s, n, r64, (const double2*)nullptr, red.partials);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_reliable_decide, dim3(1), dim3(256), 0, s, nb, red.partials, st, red.mbox);
+hipError_t launch_reliable_decide(int nblk, Reduce red, SolverState* st, hipStream_t s) {
+  if (nblk > red.capacity) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_reliable_decide, dim3(1), dim3(1024), 0, s, nblk, red.partials, st, red.mbox);
   return hipGetLastError();
 }
 

@@ -247,6 +247,41 @@ struct EpiShiftResidual {
   __device__ void tail() const {}
 };
 
+// Last hop of r = phi - Mhat^dag Mhat x (odd sites), block partials of |r|^2:
+// the subtraction and the norm of a reliable update were two passes over the
+// field (24^3x48: 29 + 13 us, of 93 beside the update's hops).
+struct EpiSchurResidual {
+  using P = Planes<double, double2>;
+  static constexpr bool kReduce = true;
+  static constexpr bool kPrefetch = true;
+  const double2* w;
+  const double2* phi;
+  double2* r;
+  double coef;
+  int vh;
+  __device__ bool skip() const { return false; }
+  struct Pre {
+    C<double> w[3], f[3];
+  };
+  __device__ Pre pre(int, int cb, int own) const {
+    Pre q;
+    P::ld(w, vh, own, cb, q.w);
+    P::ld(phi, vh, own, cb, q.f);
+    return q;
+  }
+  __device__ void apply(int, int cb, int own, const C<double>* acc, double& red, const Pre& q) const {
+    C<double> v[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      v[i] = q.f[i] - (q.w[i] + coef * acc[i]);
+      red += norm2(v[i]);
+    }
+    P::st(r, vh, own, cb, v);
+  }
+  template <int NT>
+  __device__ void tail() const {}
+};
+
 template <typename R, typename T>
 struct EpiSchurNorm {  // w = x + coef * acc (odd sites), block partials of |w|^2 (of w as stored)
   static constexpr bool kReduce = true;
@@ -633,6 +668,15 @@ hipError_t launch_hop_shift_residual(const Geom& g, HopIn<double> hin, const dou
   return launch<double, true>(g, 1, hin, EpiShiftResidual{w, x, phi, sigma, coef, g.vs}, partials, s,
                               hop_blocks(g, 1));
 }
+template <bool DAG>
+hipError_t launch_hop_schur_residual(const Geom& g, HopIn<double> hin, const double2* w, const double2* phi,
+                                     double2* r, double coef, Reduce red, hipStream_t s) {
+  return launch<double, DAG>(g, 1, hin, EpiSchurResidual{w, phi, r, coef, g.vs}, red.partials, s, red.capacity);
+}
+template hipError_t launch_hop_schur_residual<false>(const Geom&, HopIn<double>, const double2*, const double2*,
+                                                     double2*, double, Reduce, hipStream_t);
+template hipError_t launch_hop_schur_residual<true>(const Geom&, HopIn<double>, const double2*, const double2*,
+                                                    double2*, double, Reduce, hipStream_t);
 template hipError_t launch_hop_step<double, false>(const Geom&, const double2*, int, double2*, double2*,
                                                    const double2*, SolverState*, Reduce, hipStream_t);
 template hipError_t launch_hop_step<double, true>(const Geom&, const double2*, int, double2*, double2*,

@@ -209,7 +209,8 @@ __global__ __launch_bounds__(kPairThreads) void k_hop_pair(Geom g, const R2<R>* 
   M3<R> U = load_rows<R>(gauge, nk, g, bwd ? 1 : 0, mu, bwd ? nb : cbe);
 
   // ---- every other load but the second hop's input
-  if (tid == 0) s_done = st->done;  // once a block: block 0 of this launch may set it meanwhile
+  const int found = st->done;
+  if (tid == 0) s_done = found;  // one decision a block: block 0 of this launch may set it meanwhile
   const double rr_in = MODE == kPairSecond ? st->rr : st->rr_prev;
   const int iter_in = MODE == kPairSecond ? st->iter : st->iter_prev;
   const double rr_max0 = st->rr_max, rr_stop = st->rr_stop, delta2 = st->delta2;
@@ -252,6 +253,15 @@ __global__ __launch_bounds__(kPairThreads) void k_hop_pair(Geom g, const R2<R>* 
       }
     }
   }
+
+  // A stopped solve is left here, behind the loads, where no block of this
+  // launch can have set what was found (the waves of a block would part
+  // otherwise).
+  asm volatile("" ::: "memory");
+  if (MODE == kPairFresh ? found != kDoneRunning
+      : MODE == kPairStep ? found == kDoneUpdateHeld && lb != 0
+                          : found != kDoneRunning && found != kDoneBreakdown)
+    return;
 
   // ---- first hop
   switch (mu) {

@@ -209,6 +209,11 @@ hipError_t launch_hop_direction(const Geom& g, const double2* gauge, int nk, dou
 hipError_t launch_hop_shift_residual(const Geom& g, HopIn<double> hin, const double2* w, const double2* x,
                                      const double2* phi, double sigma, double coef, double* partials,
                                      hipStream_t s);
+// r = phi - (w + coef H in) on odd sites, the last hop of a Schur residual;
+// leaves hop_blocks(g, 1) block partials of |r|^2
+template <bool DAG>
+hipError_t launch_hop_schur_residual(const Geom& g, HopIn<double> hin, const double2* w, const double2* phi,
+                                     double2* r, double coef, Reduce red, hipStream_t s);
 // Residual of the full operator: r = phi - (self + coef * H in) over both parities,
 // result[slot] = |r|^2
 template <bool DAG>
@@ -265,7 +270,7 @@ hipError_t launch_compress_links(const Geom& g, const double2* U64, double2* Uc,
 //   launch_rescale_residual_dev: as launch_rescale_residual with sigma,
 //     restart and bscale from the state, and only if it is running
 hipError_t launch_mixed_fold(int vs, float2* xs, double2* x, const SolverState* st, hipStream_t s);
-hipError_t launch_reliable_decide(int n, const double2* r64, Reduce red, SolverState* st, hipStream_t s);
+hipError_t launch_reliable_decide(int nblk, Reduce red, SolverState* st, hipStream_t s);
 template <typename T>
 hipError_t launch_rescale_residual_dev(int vs, const double2* r64, float2* r, T* p, const SolverState* st,
                                        hipStream_t s);
