@@ -279,8 +279,10 @@ template <typename R, typename T>
 __global__ __launch_bounds__(kStepThreads) void k_cg_step(int n, int vs, int nblk, const double* __restrict__ partials,
                                                           const R2<R>* __restrict__ r, T* __restrict__ p,
                                                           SolverState* st, Mailbox* mb, R2<R>* __restrict__ x) {
-  const int done0 = st->done;
-  if (done0 != kDoneRunning) {  // the iteration was skipped (or block 0 below already stopped it)
+  // what the third hop recorded: done itself is block 0's to set below, while
+  // other blocks may only be starting
+  const int done0 = st->done_prev;
+  if (done0 != kDoneRunning) {  // the iteration was skipped
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       if (done0 == kDoneUpdate) st->done = kDoneUpdateHeld;
       // the same action as the stop itself, in case the host has not seen it

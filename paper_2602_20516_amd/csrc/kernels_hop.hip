@@ -43,7 +43,11 @@ struct EpiAxpy {  // out = self + coef * acc
   // of Mhat^dag Mhat, which need no scalar).
   const double* pap_partials;
   int pap_nblk;
-  __device__ bool skip() const { return guard && guard->done != kDoneRunning; }
+  __device__ bool skip() const {
+    if (!guard || guard->done == kDoneRunning) return false;
+    if (pap_partials && blockIdx.x == 0 && threadIdx.x == 0) guard->done_prev = guard->done;
+    return true;
+  }
   using P = Planes<R, T>;
   static constexpr int NC = P::NC;
   struct Pre {
@@ -73,8 +77,10 @@ struct EpiAxpy {  // out = self + coef * acc
       if (!(pap > 0.0) || !isfinite(pap)) {
         guard->alpha = 0.0;
         guard->done = kDoneBreakdown;
+        guard->done_prev = kDoneBreakdown;
       } else {
         guard->alpha = guard->rr / pap;
+        guard->done_prev = kDoneRunning;
       }
     }
   }
@@ -112,7 +118,9 @@ struct EpiStep {
   __device__ bool skip() const {  // block-collective: every thread of the block calls it
     __shared__ int s_run;
     SolverState* st = state;
-    const int done0 = st->done;
+    // what the third hop recorded: done itself is block 0's to set below, while
+    // other blocks, or waves of them, may only be starting
+    const int done0 = st->done_prev;
     if (done0 != kDoneRunning) {
       if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (done0 == kDoneUpdate) st->done = kDoneUpdateHeld;

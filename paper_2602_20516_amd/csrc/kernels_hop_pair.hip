@@ -209,8 +209,13 @@ __global__ __launch_bounds__(kPairThreads) void k_hop_pair(Geom g, const R2<R>* 
   M3<R> U = load_rows<R>(gauge, nk, g, bwd ? 1 : 0, mu, bwd ? nb : cbe);
 
   // ---- every other load but the second hop's input
-  const int found = st->done;
-  if (tid == 0) s_done = found;  // one decision a block: block 0 of this launch may set it meanwhile
+  // Stopped or not: the step takes what the second launch of its iteration
+  // recorded (done itself is block 0's to set below, while other blocks may
+  // only be starting); in the second launch block 0 may set a breakdown
+  // meanwhile, so one thread reads for its block.
+  const int found = MODE == kPairStep ? st->done_prev : st->done;
+  if (tid == 0) s_done = found;
+  const bool rec = lb == 0 && tid == 0;
   const double rr_in = MODE == kPairSecond ? st->rr : st->rr_prev;
   const int iter_in = MODE == kPairSecond ? st->iter : st->iter_prev;
   const double rr_max0 = st->rr_max, rr_stop = st->rr_stop, delta2 = st->delta2;
@@ -254,14 +259,15 @@ __global__ __launch_bounds__(kPairThreads) void k_hop_pair(Geom g, const R2<R>* 
     }
   }
 
-  // A stopped solve is left here, behind the loads, where no block of this
-  // launch can have set what was found (the waves of a block would part
-  // otherwise).
-  asm volatile("" ::: "memory");
-  if (MODE == kPairFresh ? found != kDoneRunning
-      : MODE == kPairStep ? found == kDoneUpdateHeld && lb != 0
-                          : found != kDoneRunning && found != kDoneBreakdown)
+  asm volatile("" ::: "memory");  // the loads are issued before the wait for what was found
+  if (found != kDoneRunning && (MODE != kPairSecond || found != kDoneBreakdown)) {
+    if (MODE == kPairSecond && rec) st->done_prev = found;
+    if (MODE == kPairStep && rec) {
+      if (found == kDoneUpdate) st->done = kDoneUpdateHeld;
+      post_progress(a.mb, st->iter, action_word(st->epoch, found == kDoneUpdateHeld ? kDoneUpdate : found));
+    }
     return;
+  }
 
   // ---- first hop
   switch (mu) {
@@ -303,18 +309,9 @@ __global__ __launch_bounds__(kPairThreads) void k_hop_pair(Geom g, const R2<R>* 
   __syncthreads();
 
   // ---- the scalars, alike in every thread
-  const int done0 = s_done;
   R beta = 0, alpha = 0;
-  const bool rec = lb == 0 && tid == 0;
-  if constexpr (MODE == kPairStep) {
-    if (done0 != kDoneRunning) {
-      if (rec) {
-        if (done0 == kDoneUpdate) st->done = kDoneUpdateHeld;
-        post_progress(a.mb, st->iter, action_word(st->epoch, done0 == kDoneUpdateHeld ? kDoneUpdate : done0));
-      }
-      return;
-    }
-  } else if (done0 != kDoneRunning) {
+  if (MODE == kPairSecond && s_done != kDoneRunning) {
+    if (rec) st->done_prev = s_done;
     return;
   }
   if constexpr (MODE != kPairFresh) {
@@ -347,6 +344,7 @@ __global__ __launch_bounds__(kPairThreads) void k_hop_pair(Geom g, const R2<R>* 
         st->rr_prev = rr_in;
         st->iter_prev = iter_in;
         st->alpha = al;
+        st->done_prev = ok ? kDoneRunning : kDoneBreakdown;
         if (!ok) st->done = kDoneBreakdown;
       }
       alpha = R(al);

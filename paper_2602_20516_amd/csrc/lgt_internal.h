@@ -35,7 +35,7 @@ struct SolverState {
   int epoch;        // reliable updates done; tags the mailbox actions (see action_word)
   int restart;      // mixed precision: the next direction restarts from the residual
   int nupd;         // FP64 residual recomputations
-  int pad;
+  int done_prev;    // done as the third hop of the running iteration found or set it, for the step like rr_prev
 };
 
 // kDoneUpdate: the recursion stopped for an FP64 (reliable) update in this
@@ -151,7 +151,8 @@ hipError_t launch_momenta(const Geom& g, const double* normals, double2* P, hipS
 // Hop variants (kernels_hop.hip).  p_out in {0,1}: one parity; -1: both.
 // out = self + coef * H in   (self may be null); T: spinor storage type
 // guard: skip once the solve has stopped; pap_partials: block 0 also forms
-// pap and alpha from the previous launch's partials (see EpiAxpy::tail)
+// pap and alpha from the previous launch's partials (see EpiAxpy::tail) and
+// records rr, iter and done for the step
 template <typename T> struct NoDeduce { using type = T; };  // keeps nullptr arguments out of deduction
 template <typename R, bool DAG, typename T = R2<R>>
 hipError_t launch_hop_axpy(const Geom& g, int p_out, HopIn<R, T> hin, T* out_even, T* out_odd,
