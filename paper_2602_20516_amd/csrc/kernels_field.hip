@@ -21,15 +21,18 @@ namespace lgt {
 // planes runs at 5.35 TB/s with planes 2^21 elements apart and at 6.2 TB/s
 // with them a little off that distance; the two-row hops at 32^3x64 take 125
 // (FP32) and 264 us (FP64) dense, 120 and 248 us padded, the smeared force
-// there 218.7 and 209.6 ms.  Planes of more than 131072 sites that are a
-// multiple of 16384 are therefore 2112 = 33 * 64 sites further apart (64,
-// 1088 and 4160 measured within 1 %).  Others stay dense: at 24^3x48 (81 *
-// 2^12 sites) the padding gave the FP64 hop 4 % and cost the smearing 0.6 %,
-// and fields that stay in the caches (16^4 and below) gain nothing.  A lattice
+// there 218.7 and 209.6 ms.  In the caches the same holds for L2 channels, and
+// dense fields of 16^4 come out in one of two ways from process to process
+// (mixed FP32 force 5.27 or 5.51 ms; padded 5.16 to 5.26; rational force 5.25
+// and 5.10 ms).  Planes of more than 16384 sites that are a multiple of 16384
+// are therefore 2112 = 33 * 64 sites further apart (64, 1088 and 4160 measured
+// within 1 %).  Others stay dense: at 24^3x48 (81 * 2^12 sites) the padding
+// gave the FP64 hop 4 % and cost the smearing 0.6 %, and 8x16^3 (16384 sites)
+// lost by it (FP64 solve 4.90 -> 4.99 ms, rational force 3.34 -> 3.42).  A lattice
 // that only fits the 32-bit field offsets without the padding (for 1..16
 // batched fields, or the gauge field of the 32-site hop blocks) stays dense
 // too, so that no call is lost to it.
-constexpr int kPadMinVh = 131072;
+constexpr int kPadMinVh = 16384;
 constexpr int kPadAlign = 16384;
 constexpr int kPadSites = 2112;
 int plane_stride(int vh) {

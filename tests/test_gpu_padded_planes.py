@@ -1,4 +1,4 @@
-"""Lattices whose packed planes are padded apart (more than 131072 sites per
+"""Lattices whose packed planes are padded apart (more than 16384 sites per
 parity, a multiple of 16384): what sums whole fields must not see the padding,
 in particular that of a batched field, which moves with the number of
 right-hand sides."""
