@@ -108,8 +108,11 @@ hipError_t launch_finalize(int mode, int nblk, Reduce red, SolverState* st, int 
 int hop_blocks(const Geom& g, int p_out);
 
 // Lattices with at most this many sites per parity run the hop with 32
-// sites per block (half-wave hops), larger ones with 64.
-constexpr int kHopHalfWaveMaxVh = 8192;
+// sites per block (half-wave hops), larger ones with 64: up to there 64-site
+// blocks leave SIMDs without a wave (solve to 1e-11, 64 against 32: FP64 12^4
+// 4.24 -> 4.10 ms, 12^2x16^2 6.40 -> 5.55, 12x16^3 7.02 -> 6.18, 16^3x14 7.26
+// -> 7.63; mixed FP32 4.00 -> 3.92, 5.02 -> 4.92, 5.12 -> 5.05, 5.12 -> 5.25).
+constexpr int kHopHalfWaveMaxVh = 24576;
 // Lattices with at most this many sites per parity run the CG iteration of
 // the FP32 and FP64 recursions as two launches of two hops each.  One box of
 // eight sites a CU is 2048; an FP64 box leaves no registers for a second one
