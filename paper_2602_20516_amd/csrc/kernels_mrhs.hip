@@ -9,8 +9,7 @@
 //
 // Hop decomposition: a 256-thread block owns 64 consecutive sites of one
 // parity and a group of G right-hand sides; wave w (= direction mu) loads
-// the two links of its direction once, keeps them in registers (FP32; FP64
-// reloads them per right-hand side to stay clear of spills) and then, for
+// the two links of its direction once, keeps them in registers and then, for
 // each right-hand side of the group in turn, computes both hops along mu,
 // meets the other waves in LDS and runs the epilogue for spin component w.
 // The link traffic is paid once per group instead of once per field, and
@@ -247,7 +246,7 @@ struct Exchange {
 };
 
 template <typename R, bool DAG, typename Epi>
-__global__ __launch_bounds__(256) void k_hop_mrhs(Geom g, int nr, int G, int nbp, int ngrp, int p_fixed,
+__global__ __launch_bounds__(256, 2) void k_hop_mrhs(Geom g, int nr, int G, int nbp, int ngrp, int p_fixed,
                                                   HopIn<R> hin, Epi epi, double* partials) {
   if (epi.skip()) return;
   // two buffers, so that one barrier a right-hand side is enough
@@ -294,11 +293,15 @@ __global__ __launch_bounds__(256) void k_hop_mrhs(Geom g, int nr, int G, int nbp
   const int nk = hin.nk;
   const BufRsrc ruf = make_rsrc(hin.gauge + (size_t)((p * 4 + mu) * nk) * g.vs, (size_t)nk * gs);
   const BufRsrc rub = make_rsrc(hin.gauge + (size_t)(((1 - p) * 4 + mu) * nk) * g.vs, (size_t)nk * gs);
-  constexpr bool kKeepLinks = sizeof(R) == 4;
+  // The links stay in registers for the whole group.  FP64 read them again for
+  // every right-hand side, 18 of its 42 loads, and the L2's return path bounds
+  // the launch: 16^4 x 12 69.6 -> 49.3 us in a mixed solve, 59 -> 35 us where
+  // all right-hand sides run; two waves a SIMD, as the exchange allows, leave
+  // 256 registers for them.
   M3<R> Uf, Ub;
 #pragma unroll
   for (int k = 0; k < 9; ++k) Uf.m[k] = Ub.m[k] = czero<R>();
-  if (kKeepLinks && active && act) {
+  if (active && act) {
     if (nk == 9) {
 #pragma unroll
       for (int k = 0; k < 9; ++k) {
@@ -323,13 +326,6 @@ __global__ __launch_bounds__(256) void k_hop_mrhs(Geom g, int nr, int G, int nbp
     for (int k = 0; k < 12; ++k) acc[k] = czero<R>();
     if (owner) pre = epi.pre(p, ps, mu, at);
     if (active) {
-      if (!kKeepLinks) {
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-          Uf.m[k] = ld_buf<R>(ruf, (unsigned)cb * E, k * gs);
-          Ub.m[k] = ld_buf<R>(rub, (unsigned)nb * E, k * gs);
-        }
-      }
       const unsigned of = in.off(nf, n), ob = in.off(nb, n);
       switch (mu) {
         case 0: hop_dir_u<R, 0, DAG>(g, Uf, Ub, in, of, ob, c, acc); break;
