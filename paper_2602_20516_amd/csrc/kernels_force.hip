@@ -319,39 +319,58 @@ hipError_t launch_bilinear_sum(const Geom& g, const double2* U, const BilinearSu
 // SIMD instead of two, by fewer registers, 1684.  The stout levels, whose
 // exponential needs the registers, lose by the exchange (one level forward at
 // 24^3x48: 480 -> 560 us) and sum their staples thread by thread.
-template <int LAYOUT>
+// SHARE false: every thread sums its staples from its own loads, without the
+// barrier that waits for the exchanged ones.
+template <int LAYOUT, bool SHARE>
 __global__ __launch_bounds__(256) void k_gauge_force_sb(Geom g, const double2* __restrict__ U, double beta,
                                                         int mode, double dt, double2* out, BlockOrder order) {
   // the shared links; for the canonical layout then the [64][36] output staging
-  __shared__ StapleLinks links;
+  constexpr size_t kStage = LAYOUT == kCanonical ? sizeof(double2) * kSB * 36 : sizeof(double2);
+  __shared__ __align__(16) char smem[SHARE ? sizeof(StapleLinks) : kStage];
+  static_assert(sizeof(StapleLinks) >= sizeof(double2) * kSB * 36, "the staging reuses the links' LDS");
   __shared__ int sh_site[kSB];
   const int lb = xcd_block(blockIdx.x, gridDim.x);
   const int p = lb & 1, blk = gauge_site_block(lb, order, g.L[2]);
   const int lane = threadIdx.x & 63, mu = wave_id();
   const int cb = blk * kSB + lane;
   const bool active = cb < g.vh;
+  const int cbx = active ? cb : 0;
   int c[4];
-  cb_coords(g, p, active ? cb : 0, c);
-  const M3<double> A = staple_block(U, g, p, active ? cb : 0, c, mu, lane, links);
-  M3<double> M;
-  if (mode == 1) M = mscale(-beta / 3.0, mdag(A));
-  else M = mscale(beta / 6.0, proj_ta(mmul(lds_link(links.own[mu], lane), A)));
-  double2 (*sh)[36] = reinterpret_cast<double2 (*)[36]>(&links);
-  static_assert(sizeof(StapleLinks) >= sizeof(double2) * kSB * 36, "the staging reuses the links' LDS");
-  if (LAYOUT == kCanonical) __syncthreads();  // every wave is done with the links
+  cb_coords(g, p, cbx, c);
+  StapleLinks& links = *reinterpret_cast<StapleLinks*>(smem);  // SHARE
+  M3<double> A, M;
+  if constexpr (SHARE) A = staple_block(U, g, p, cbx, c, mu, lane, links);
+  else A = staple_A(U, g, c, mu);
+  if (mode == 1) {
+    M = mscale(-beta / 3.0, mdag(A));
+  } else if constexpr (SHARE) {
+    M = mscale(beta / 6.0, proj_ta(mmul(lds_link(links.own[mu], lane), A)));
+  } else {
+    M = mscale(beta / 6.0, proj_ta(mmul(link_uni(U, g, p, mu, cbx), A)));
+  }
+  double2 (*sh)[36] = reinterpret_cast<double2 (*)[36]>(smem);
+  if (SHARE && LAYOUT == kCanonical) __syncthreads();  // every wave is done with the links
   emit_block<LAYOUT>(g, out, p, blk, lane, mu, mode, dt, M, active, lex_of(g, c), sh, sh_site);
 }
 
+// Up to one block a CU (8192 sites a parity) nothing is gained by the
+// exchange, and its barrier costs a round trip (8^4: 12.1 thread by thread, 12.3
+// us with it; 8^3x16 13.3 and 13.5; 12^4 22.5 and 21.3).
+constexpr int kStapleShareMinVh = 8192;
+
 hipError_t launch_gauge_force(const Geom& g, const double2* U, double beta, int mode, double dt, void* out,
                               int layout, hipStream_t s) {
-  const int nb = sb_blocks(g);
+  const dim3 nb(sb_blocks(g));
   const BlockOrder order = gauge_block_order(g);
-  if (layout == kCanonical)
-    hipLaunchKernelGGL((k_gauge_force_sb<kCanonical>), dim3(nb), dim3(256), 0, s, g, U, beta, mode, dt,
-                       (double2*)out, order);
-  else
-    hipLaunchKernelGGL((k_gauge_force_sb<kPacked>), dim3(nb), dim3(256), 0, s, g, U, beta, mode, dt,
-                       (double2*)out, order);
+  double2* o = (double2*)out;
+  const bool share = g.vh > kStapleShareMinVh;
+  if (layout == kCanonical) {
+    if (share) hipLaunchKernelGGL((k_gauge_force_sb<kCanonical, true>), nb, dim3(256), 0, s, g, U, beta, mode, dt, o, order);
+    else hipLaunchKernelGGL((k_gauge_force_sb<kCanonical, false>), nb, dim3(256), 0, s, g, U, beta, mode, dt, o, order);
+  } else {
+    if (share) hipLaunchKernelGGL((k_gauge_force_sb<kPacked, true>), nb, dim3(256), 0, s, g, U, beta, mode, dt, o, order);
+    else hipLaunchKernelGGL((k_gauge_force_sb<kPacked, false>), nb, dim3(256), 0, s, g, U, beta, mode, dt, o, order);
+  }
   return hipGetLastError();
 }
 
