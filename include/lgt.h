@@ -480,7 +480,9 @@ LGT_API lgt_status lgt_hop_benchmark_mrhs(lgt_ctx* ctx, const void* U, const voi
  * 256-thread block 64 sites, each wave both hops along one direction;
  * sites = 32 gives a block 32 sites, each half-wave one of the two hops, so
  * a small lattice runs twice as many waves.  0 (the default) takes 32 up to
- * 24576 sites per parity and 64 above.  The two shapes add the eight hop
+ * 24576 sites per parity and 64 above.  0 also lets the smallest
+ * lattices (3072 sites per parity with FP32 vectors, 2048 with FP64) run a CG
+ * iteration as two launches of two hops each.  The two shapes add the eight hop
  * terms of a site in different orders, so results may differ by rounding;
  * each is deterministic.  INVALID_ARGUMENT for any other value, and for 32
  * on a lattice whose FP64 gauge field is 4 GiB or more (V above 7456540). */

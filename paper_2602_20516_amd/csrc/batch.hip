@@ -200,22 +200,24 @@ struct BatchSolver {
                                        red(), mask)));
   }
 
-  // out = Mhat^dag Mhat x (FP64) for the right-hand sides with mask[n] != 0
-  // (all if mask is null; the others' out is left as it was), scratch: even
-  // half of bW0, odd half of bW4
-  void apply_normal64(bool dag, const double2* x, double2* out, const double* mask = nullptr) {
+  // r = phi - Mhat^dag Mhat x (FP64) and result[n] = |r_n|^2 for the right-hand
+  // sides with mask[n] != 0 (the others' r is left as it was, their result 0),
+  // scratch: even half of bW0, odd half of bW4
+  void residual64(bool dag, const double2* x, const double2* phi, double2* r, const double* mask) {
     double2* t = F(bW0);
     double2* wv = F(bW4) + halfn();
     if (!dag) {
       mhop<double, false>(0, c->U64, x, t, nullptr, vec(vOne), nullptr, nullptr, mask);
       mhop<double, false>(1, c->U64, t, wv, x, vec(vMK2), nullptr, nullptr, mask);
       mhop<double, true>(0, c->U64, wv, t, nullptr, vec(vOne), nullptr, nullptr, mask);
-      mhop<double, true>(1, c->U64, t, out, wv, vec(vMK2), nullptr, nullptr, mask);
+      LGT_HIP(launch_mhop_schur_residual<true>(c->g, nr, gsize<double>(), HopIn<double>{c->U64, t, t}, wv, phi, r,
+                                               vec(vMK2), mask, red(), c->stream));
     } else {
       mhop<double, true>(0, c->U64, x, t, nullptr, vec(vOne), nullptr, nullptr, mask);
       mhop<double, true>(1, c->U64, t, wv, x, vec(vMK2), nullptr, nullptr, mask);
       mhop<double, false>(0, c->U64, wv, t, nullptr, vec(vOne), nullptr, nullptr, mask);
-      mhop<double, false>(1, c->U64, t, out, wv, vec(vMK2), nullptr, nullptr, mask);
+      LGT_HIP(launch_mhop_schur_residual<false>(c->g, nr, gsize<double>(), HopIn<double>{c->U64, t, t}, wv, phi, r,
+                                                vec(vMK2), mask, red(), c->stream));
     }
   }
 
@@ -331,9 +333,7 @@ struct BatchSolver {
       }
       upload_vecs();
       LGT_HIP(launch_mmixed_update(c->vs, nr, xs, z, vec(vScale), c->stream));
-      apply_normal64(dag, z, r64, vec(vUnverified));
-      LGT_HIP(launch_xmy64((int)n, rhs, r64, c->stream));
-      LGT_HIP(launch_mnorm<double>(c->vh, c->vs, 12, nr, r64, red(), c->stream));
+      residual64(dag, z, rhs, r64, vec(vUnverified));
       read_results(nr);
       bool all = true;
       for (int k = 0; k < nr; ++k) {

@@ -409,20 +409,6 @@ hipError_t launch_copy64(int n, const double2* x, double2* y, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_xmy64(int n, const double2* __restrict__ x, double2* __restrict__ y) {
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-    const double2 xv = x[i];
-    double2 yv = y[i];
-    yv.x = xv.x - yv.x;
-    yv.y = xv.y - yv.y;
-    y[i] = yv;
-  }
-}
-hipError_t launch_xmy64(int n, const double2* x, double2* y, hipStream_t s) {
-  hipLaunchKernelGGL(k_xmy64, dim3((n + 255) / 256), dim3(256), 0, s, n, x, y);
-  return hipGetLastError();
-}
-
 __global__ __launch_bounds__(256) void k_zero64(int n, double2* __restrict__ y) {
   for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) y[i] = make_double2(0.0, 0.0);
 }

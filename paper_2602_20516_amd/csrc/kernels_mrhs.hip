@@ -168,7 +168,7 @@ struct MEpiSchurCG {  // q = w + coef_n acc; r -= alpha_n q (unless converged)
   __device__ void tail(int) const {}
 };
 
-struct MEpiResidual {  // r = phi - (self + coef_n acc), per-RHS |r|^2 (both parities, FP64)
+struct MEpiResidual {  // r = phi - (self + coef_n acc), per-RHS |r|^2 (FP64)
   static constexpr bool kReduce = true;
   using P = Planes<double, double2>;
   static constexpr int NC = P::NC;
@@ -176,8 +176,9 @@ struct MEpiResidual {  // r = phi - (self + coef_n acc), per-RHS |r|^2 (both par
   const double2* phi[2];
   double2* r[2];
   const double* coef;
+  const double* mask;  // if set, only right-hand sides with a nonzero entry
   __device__ bool skip() const { return false; }
-  __device__ bool rhs_active(int) const { return true; }
+  __device__ bool rhs_active(int n) const { return !mask || mask[n] != 0.0; }
   struct Pre {
     C<double> f[NC], s[NC];
   };
@@ -681,9 +682,21 @@ hipError_t launch_mhop_residual(const Geom& g, int nr, int G, HopIn<double> hin,
   e.r[0] = r_full;
   e.r[1] = r_full + half;
   e.coef = coef;
+  e.mask = nullptr;
   hipError_t err = mlaunch<double, DAG>(g, nr, G, -1, hin, e, red, s);
   if (err != hipSuccess) return err;
   return launch_mfinalize(kFinResult1, 2 * mrhs_nbp(g, G), nr, red, nullptr, 0.0, 0, s);
+}
+// (subtraction and norm were passes of their own: 16^4 x 12 46 + 33 us beside
+// four hops of 49 us)
+template <bool DAG>
+hipError_t launch_mhop_schur_residual(const Geom& g, int nr, int G, HopIn<double> hin, const double2* w,
+                                      const double2* phi, double2* r, const double* coef, const double* mask,
+                                      Reduce red, hipStream_t s) {
+  const MEpiResidual e{{nullptr, w}, {nullptr, phi}, {nullptr, r}, coef, mask};
+  hipError_t err = mlaunch<double, DAG>(g, nr, G, 1, hin, e, red, s);
+  if (err != hipSuccess) return err;
+  return launch_mfinalize(kFinResult1, mrhs_nbp(g, G), nr, red, nullptr, 0.0, 0, s);
 }
 
 #define LGT_INST_MHOP(R, DAG)                                                                                   \
@@ -699,6 +712,12 @@ LGT_INST_MHOP(double, false)
 LGT_INST_MHOP(double, true)
 LGT_INST_MHOP(float, false)
 LGT_INST_MHOP(float, true)
+template hipError_t launch_mhop_schur_residual<false>(const Geom&, int, int, HopIn<double>, const double2*,
+                                                      const double2*, double2*, const double*, const double*, Reduce,
+                                                      hipStream_t);
+template hipError_t launch_mhop_schur_residual<true>(const Geom&, int, int, HopIn<double>, const double2*,
+                                                     const double2*, double2*, const double*, const double*, Reduce,
+                                                     hipStream_t);
 template hipError_t launch_mhop_residual<false>(const Geom&, int, int, HopIn<double>, const double2*,
                                                 const double2*, double2*, const double*, Reduce, hipStream_t);
 template hipError_t launch_mhop_residual<true>(const Geom&, int, int, HopIn<double>, const double2*,

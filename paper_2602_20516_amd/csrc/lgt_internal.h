@@ -249,7 +249,6 @@ hipError_t launch_norm_dot(int n, const double2* a, const double2* b, Reduce red
                            hipStream_t s);
 hipError_t launch_axpy64(int n, double a, const double2* x, double2* y, hipStream_t s);  // y += a x
 hipError_t launch_copy64(int n, const double2* x, double2* y, hipStream_t s);
-hipError_t launch_xmy64(int n, const double2* x, double2* y, hipStream_t s);             // y = x - y
 hipError_t launch_zero64(int n, double2* y, hipStream_t s);
 hipError_t launch_zero32(int n, float2* y, hipStream_t s);
 hipError_t launch_convert_64_32(int n, const double2* x, float2* y, hipStream_t s);  // links: same planes

@@ -51,6 +51,12 @@ template <bool DAG>
 hipError_t launch_mhop_residual(const Geom& g, int nr, int G, HopIn<double> hin, const double2* self_full,
                                 const double2* phi_full, double2* r_full, const double* coef, Reduce red,
                                 hipStream_t s);
+// The same on odd sites, the last hop of a Schur residual (half fields): only
+// the right-hand sides of a nonzero mask entry, 0 for the others
+template <bool DAG>
+hipError_t launch_mhop_schur_residual(const Geom& g, int nr, int G, HopIn<double> hin, const double2* w,
+                                      const double2* phi, double2* r, const double* coef, const double* mask,
+                                      Reduce red, hipStream_t s);
 
 // result[n] = |a_n|^2 over a multi-RHS field of ncomp components (12 half, 24 full)
 template <typename R>
