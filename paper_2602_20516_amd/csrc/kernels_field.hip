@@ -526,8 +526,13 @@ __global__ __launch_bounds__(1024) void k_reliable_decide(int nblk, const double
     code = kDoneFailed;
   } else if (rr64 <= st->rr_target) {
     code = kDoneConverged;
+  } else if (entry == kDoneBreakdown && st->restart && st->iter == st->iter_upd) {
+    code = kDoneFailed;  // nothing has moved since that restart: another one would repeat it, without end
+  } else if (entry == kDoneBreakdown && st->iter >= st->max_iter) {
+    code = kDoneMaxIter;  // the recursion looks at the cap only in iterations that do not break down
   } else {
     const double sn = 1.0 / sqrt(rr64);
+    st->iter_upd = st->iter;
     st->restart = entry == kDoneBreakdown;
     st->bscale = st->beta * sn / st->sigma;
     st->sigma = sn;

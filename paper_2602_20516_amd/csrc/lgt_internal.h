@@ -35,6 +35,7 @@ struct SolverState {
   int epoch;        // reliable updates done; tags the mailbox actions (see action_word)
   int restart;      // mixed precision: the next direction restarts from the residual
   int nupd;         // FP64 residual recomputations
+  int iter_upd;     // iter at the last of them that went on (0: at the start)
   int done_prev;    // done as the third hop of the running iteration found or set it, for the step like rr_prev
 };
 
@@ -44,7 +45,9 @@ struct SolverState {
 // into kDoneUpdateHeld, which no kernel touches.
 enum { kDoneRunning = 0, kDoneConverged = 1, kDoneMaxIter = 2, kDoneBreakdown = 3, kDoneUpdate = 4,
        kDoneUpdateHeld = 5, kDoneFailed = 6 };
-// kDoneFailed: the FP64 residual of a reliable update is not finite.
+// kDoneFailed: the FP64 residual of a reliable update is not finite, or the
+// recursion broke down on the residual itself as its direction, so that a
+// restart would only break down again.
 
 // Output layout of the gauge-type kernels (forces, link update).
 enum Layout { kCanonical = 0, kPacked = 1 };
@@ -265,7 +268,9 @@ hipError_t launch_compress_links(const Geom& g, const double2* U64, double2* Uc,
 // Device-side reliable update, enqueued without a host round trip:
 //   launch_mixed_fold:       x += xs / st->sigma; xs = 0
 //   launch_reliable_decide:  |r64|^2 (deterministic two-launch reduction),
-//     then: not finite -> kDoneFailed; <= rr_target -> kDoneConverged; else
+//     then: not finite -> kDoneFailed; <= rr_target -> kDoneConverged; a
+//     breakdown in the first iteration after a restart (or after the start)
+//     -> kDoneFailed, another one at the iteration cap -> kDoneMaxIter; else
 //     new units sigma = 1 / |r64|, restart flag (the recursion broke down),
 //     bscale = beta sigma_new / sigma_old, the recursion's state reset
 //     (rr = rr_max = 1, rr_stop = rr_target sigma^2), kDoneRunning; epoch

@@ -269,6 +269,7 @@ int lgt_ctx::cg_normal_mixed(bool dag, double2* z, const double2* rhs, double to
   s.sigma = sigma;
   s.rr_target = rr_target;
   s.max_iter = max_iter;
+  s.restart = 1;  // p = r
   s.done = kDoneRunning;
   *host_state = s;
   LGT_HIP(hipMemcpyAsync(state, host_state, sizeof(SolverState), hipMemcpyHostToDevice, stream));
