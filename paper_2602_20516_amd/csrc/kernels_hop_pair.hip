@@ -347,6 +347,7 @@ __global__ __launch_bounds__(kPairThreads) void k_hop_pair(Geom g, const R2<R>* 
         st->done_prev = ok ? kDoneRunning : kDoneBreakdown;
         if (!ok) st->done = kDoneBreakdown;
       }
+      if (!ok) return;  // x and r stay as they were (0 times a non-finite p or q is not 0), in every block
       alpha = R(al);
     }
   }
