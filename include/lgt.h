@@ -428,8 +428,10 @@ LGT_API lgt_status lgt_cg_solve_batch(lgt_batch* b, int32_t n, const lgt_batch_i
  * ||phi_o|| over the shifts, NOT_CONVERGED if it exceeds tol (or max_iter
  * was reached).  FP64 only: other precisions return UNSUPPORTED.
  * INVALID_ARGUMENT for a null pointer, a negative or non-finite shift, or
- * nshift outside 1..32.  Holds 2 * nshift FP64 half spinors of workspace
- * on the context, kept until it is destroyed or a larger nshift is asked. */
+ * nshift outside 1..32.  Holds 2 * nshift + 2 FP64 half spinors of workspace
+ * on the context, kept until it is destroyed or a larger nshift is asked, and
+ * up to seven more, while an eighth of the device memory stays free beside
+ * them (they save memory traffic; the results have the same bits without). */
 LGT_API lgt_status lgt_cg_solve_multishift(lgt_ctx* ctx, const void* U, const void* phi, double kappa,
                                            int32_t nshift, const double* shifts, void* const* X,
                                            const lgt_solver_params* params, lgt_solver_stats* stats);

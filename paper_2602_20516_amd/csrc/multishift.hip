@@ -243,22 +243,35 @@ static MultiShiftWork* mshift_work(lgt_ctx* c, int ns) {
     LGT_HIP(hipHostMalloc(&w->hsums, (size_t)4 * ns * sizeof(double), hipHostMallocDefault));
     LGT_HIP(hipMalloc(&w->ss, sizeof(ShiftState)));
     LGT_HIP(hipHostMalloc(&w->hss, sizeof(ShiftState), hipHostMallocDefault));
-    // the ring takes what memory is left, down to one residual
-    for (; w->group < kGroup; ++w->group) {
-      const hipError_t e = hipMalloc(&w->ring.r[w->group], hb);
-      if (e == hipErrorOutOfMemory && w->group > 0) {
-        (void)hipGetLastError();
-        break;
-      }
-      LGT_HIP(e);
-      LGT_HIP(hipMemsetAsync(w->ring.r[w->group], 0, hb, c->stream));
-    }
+    LGT_HIP(hipMalloc(&w->ring.r[0], hb));
+    w->group = 1;
+    LGT_HIP(hipMemsetAsync(w->ring.r[0], 0, hb, c->stream));
   } catch (...) {
     lgt_ctx_free_multishift(c);
     throw;
   }
   w->ns = ns;
   return w;
+}
+
+// Residuals of the ring beyond the first, which only save traffic: taken once
+// everything else that the call allocates is there, and only while an eighth
+// of the device memory stays free for what comes after it (the reserve of the
+// smearing's checkpoints).  The results have the same bits for any number.
+static void grow_ring(lgt_ctx* c, MultiShiftWork* w) {
+  const size_t hb = c->half_elems() * sizeof(double2);
+  for (; w->group < kGroup; ++w->group) {
+    size_t avail = 0, total = 0;
+    LGT_HIP(hipMemGetInfo(&avail, &total));
+    if (avail < total / 8 + hb) return;
+    const hipError_t e = hipMalloc(&w->ring.r[w->group], hb);
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      return;
+    }
+    LGT_HIP(e);
+    LGT_HIP(hipMemsetAsync(w->ring.r[w->group], 0, hb, c->stream));
+  }
 }
 
 int lgt_ctx_max_shifts() { return kMaxShift; }
@@ -298,11 +311,16 @@ SolveStats lgt_ctx::solve_multishift(const double2* phi, int ns, const double* s
     st.true_res = 0.0;
     return st;
   }
-  const int m = w->group;
   double2* p = w->p;
-  double2* t = f64(kW0);      // even-half scratch, as the FP64 CG's: H p, kept for the next iteration
-  double2* t2 = f64(kW1);
+  double2* t = f64(kW0);  // even-half scratch, as the FP64 CG's: H p, kept for the next iteration
+  double2* t2 = t + h;
   double2* wv = f64(kW4) + h;  // odd-half scratch, as the FP64 CG's
+  // the recursion's hops read two-row links when the links are SU(3) to FP64
+  // rounding, as the single-shift FP64 CG's; the true residuals below use the
+  // full links
+  compress_links64();
+  grow_ring(this, w);
+  const int m = w->group;
   const int nb = std::min((n + 255) / 256, 2048);
   hipLaunchKernelGGL(k_msinit, dim3(nb), dim3(256), 0, stream, n, ns, phio, w->ring.r[m - 1], p, w->X, w->Pn);
   LGT_HIP(hipGetLastError());
@@ -329,10 +347,6 @@ SolveStats lgt_ctx::solve_multishift(const double2* phi, int ns, const double* s
   LGT_HIP(hipMemcpyAsync(state, host_state, sizeof(SolverState), hipMemcpyHostToDevice, stream));
   const double k2 = -kappa * kappa;
   const Reduce rd = red();
-  // the recursion's hops read two-row links when the links are SU(3) to FP64
-  // rounding, as the single-shift FP64 CG's; the true residuals below use the
-  // full links
-  compress_links64();
   sync();
   const int nk = host_flags[2] == 0 ? 6 : 9;
   const double2* links = nk == 6 ? U64c : U64;
@@ -378,11 +392,12 @@ SolveStats lgt_ctx::solve_multishift(const double2* phi, int ns, const double* s
   // true residuals phi_o - (A + sigma_i) X_i with the full links, all norms read back at once
   const int nres = hop_blocks(g, 1);
   // the force's fields of a group of terms: in the shifts' directions, which
-  // are done with, three halves a term (fewer than three shifts: in scratch)
-  const int gc = force ? std::min(kBilinearTerms, std::max(1, ns / 3)) : 1;
-  double2* xe = !force ? t : ns < 3 ? f64(kStageA) : w->Pn;
-  double2* yo = !force ? wv : ns < 3 ? f64(kE) + h : w->Pn + gc * h;
-  double2* ae = !force ? t2 : ns < 3 ? f64(kE) : w->Pn + 2 * gc * h;
+  // are done with, three halves a term (fewer than three shifts: in the scratch)
+  const bool in_dirs = force && ns >= 3;
+  const int gc = in_dirs ? std::min(kBilinearTerms, ns / 3) : 1;
+  double2* xe = in_dirs ? w->Pn : t;
+  double2* yo = in_dirs ? w->Pn + gc * h : wv;
+  double2* ae = in_dirs ? w->Pn + 2 * gc * h : t2;
   for (int i0 = 0; i0 < ns; i0 += gc) {
     const int c = std::min(gc, ns - i0);
     for (int i = 0; i < c; ++i) {
