@@ -144,9 +144,8 @@ struct lgt_ctx {
   // whose result (host_flags[1] == 0) is valid after the caller's next sync.
   void compress_links();
   // The same for U64 (host_flags[2] == 0: its links are SU(3) to FP64
-  // rounding).  A copy that is not required is only made while a quarter of
-  // the device memory is free; false, with nothing enqueued, if not.
-  bool compress_links64(bool required = true);
+  // rounding).
+  void compress_links64();
   void ensure_p64();
 
   // solver (solver.hip)
@@ -249,5 +248,5 @@ struct lgt_ctx {
   template <typename T>  // storage of the FP32 recursion's t, w, p: float2 or lgt::Bf16c
   int cg_normal_mixed(bool dag, double2* z, const double2* rhs, double tol, int max_iter, double delta,
                       lgt::SolveStats& st);
-  void schur_residual64(bool dag, const double2* links, int nk, const double2* x, const double2* phi, double2* r);
+  void schur_residual64(bool dag, const double2* x, const double2* phi, double2* r);
 };

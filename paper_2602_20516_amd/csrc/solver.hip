@@ -60,19 +60,11 @@ void lgt_ctx::compress_links() {
   LGT_HIP(hipMemcpyAsync(host_flags + 1, flags + 1, sizeof(int), hipMemcpyDeviceToHost, stream));
 }
 
-bool lgt_ctx::compress_links64(bool required) {
-  if (!U64c) {
-    size_t avail = 0, total = 0;
-    if (!required) {
-      LGT_HIP(hipMemGetInfo(&avail, &total));
-      if (avail < total / 4) return false;
-    }
-    LGT_HIP(hipMalloc(&U64c, (size_t)48 * vs * sizeof(double2)));
-  }
+void lgt_ctx::compress_links64() {
+  if (!U64c) LGT_HIP(hipMalloc(&U64c, (size_t)48 * vs * sizeof(double2)));
   LGT_HIP(hipMemsetAsync(flags + 2, 0, sizeof(int), stream));
   LGT_HIP(launch_compress_links(g, U64, U64c, flags + 2, stream));
   LGT_HIP(hipMemcpyAsync(host_flags + 2, flags + 2, sizeof(int), hipMemcpyDeviceToHost, stream));
-  return true;
 }
 
 void lgt_ctx::ensure_p64() {
@@ -98,28 +90,27 @@ void lgt_ctx::dslash_full(const double2* in, double2* out, double k, bool dag) {
 
 template <typename R, bool DAG>
 static void hop(const Geom& g, int p_out, const R2<R>* gauge, const R2<R>* in, R2<R>* out, const R2<R>* self,
-                double coef, hipStream_t s, int nk = 9) {
-  HopIn<R> hin{gauge, in, in, nk};
+                double coef, hipStream_t s) {
+  HopIn<R> hin{gauge, in, in};
   LGT_HIP((launch_hop_axpy<R, DAG>(g, p_out, hin, out, out, self, self, coef, s)));
 }
 
-// r_o = phi_o - Mhat^dag Mhat x_o in FP64 (4 hops on the given links), using
+// r_o = phi_o - Mhat^dag Mhat x_o in FP64 (4 hops on the full links), using
 // kW0's even half as scratch; leaves the block partials of |r_o|^2.
-void lgt_ctx::schur_residual64(bool dag, const double2* links, int nk, const double2* x, const double2* phi,
-                               double2* r) {
+void lgt_ctx::schur_residual64(bool dag, const double2* x, const double2* phi, double2* r) {
   const double k2 = -kappa * kappa;
   double2* t = f64(kW0);                 // even half
   double2* w = f64(kW4) + half_elems();  // odd half (not used by the mixed CG)
   if (!dag) {
-    hop<double, false>(g, 0, links, x, t, nullptr, 1.0, stream, nk);
-    hop<double, false>(g, 1, links, t, w, x, k2, stream, nk);
-    hop<double, true>(g, 0, links, w, t, nullptr, 1.0, stream, nk);
-    LGT_HIP(launch_hop_schur_residual<true>(g, HopIn<double>{links, t, t, nk}, w, phi, r, k2, red(), stream));
+    hop<double, false>(g, 0, U64, x, t, nullptr, 1.0, stream);
+    hop<double, false>(g, 1, U64, t, w, x, k2, stream);
+    hop<double, true>(g, 0, U64, w, t, nullptr, 1.0, stream);
+    LGT_HIP(launch_hop_schur_residual<true>(g, HopIn<double>{U64, t, t}, w, phi, r, k2, red(), stream));
   } else {
-    hop<double, true>(g, 0, links, x, t, nullptr, 1.0, stream, nk);
-    hop<double, true>(g, 1, links, t, w, x, k2, stream, nk);
-    hop<double, false>(g, 0, links, w, t, nullptr, 1.0, stream, nk);
-    LGT_HIP(launch_hop_schur_residual<false>(g, HopIn<double>{links, t, t, nk}, w, phi, r, k2, red(), stream));
+    hop<double, true>(g, 0, U64, x, t, nullptr, 1.0, stream);
+    hop<double, true>(g, 1, U64, t, w, x, k2, stream);
+    hop<double, false>(g, 0, U64, w, t, nullptr, 1.0, stream);
+    LGT_HIP(launch_hop_schur_residual<false>(g, HopIn<double>{U64, t, t}, w, phi, r, k2, red(), stream));
   }
 }
 
@@ -237,19 +228,14 @@ int lgt_ctx::cg_normal_mixed(bool dag, double2* z, const double2* rhs, double to
   double2* r64 = f64(kW2) + half_elems();
   LGT_HIP(launch_zero64(n, z, stream));
   compress_links();
-  const bool two_rows64 = g.vh > kFuseStepMaxVh && compress_links64(false);
   LGT_HIP(launch_norm_dot(n, rhs, nullptr, red(), 0, stream));
   read_results(2);
   // the inner hops read two-row links when the links are SU(3) (the third
-  // row is rebuilt in registers: a third less link traffic).  So do the FP64
-  // residuals of the reliable updates where the links are SU(3) to FP64
-  // rounding and, above the volume where hops leave the caches, the copy
-  // costs less than it saves (24^3x48: 108 -> 92 us a hop, some 70 of them in
-  // a force, 0.11 ms a copy; 32^3x64: 350 -> 295 us and 0.39 ms); the caller's
-  // check of the solution always uses the full links.
-  const bool c64 = two_rows64 && host_flags[2] == 0;
-  const double2* links64 = c64 ? U64c : U64;
-  const int nk64 = c64 ? 6 : 9;
+  // row is rebuilt in registers: a third less link traffic); the FP64
+  // residuals of the reliable updates always use the full FP64 links.  (A
+  // two-row copy for these too saved 1 to 2 % of a force past the caches, but
+  // its third rows may be off by 1e-14, and to make the copy only where memory
+  // allows made the bits depend on what else holds memory.)
   const bool c12 = host_flags[1] == 0;
   const float2* links = c12 ? U32c : U32;
   const int nk = c12 ? 6 : 9;
@@ -302,7 +288,7 @@ int lgt_ctx::cg_normal_mixed(bool dag, double2* z, const double2* rhs, double to
     const int code = (int)(act & 0xffu);
     if (code == kDoneUpdate || code == kDoneUpdateHeld || code == kDoneBreakdown) {
       LGT_HIP(launch_mixed_fold(vs, xs, z, state, stream));
-      schur_residual64(dag, links64, nk64, z, rhs, r64);
+      schur_residual64(dag, z, rhs, r64);
       LGT_HIP(launch_reliable_decide(hop_blocks(g, 1), red(), state, stream));
       LGT_HIP(launch_rescale_residual_dev<T>(vs, r64, rs, ps, state, stream));
       min_epoch = (act >> 8) + 1;
@@ -447,7 +433,7 @@ SolveStats lgt_ctx::solve_eo(const double2* phi, double2* X, double2* A, const S
   double2* e = f64(kE) + h;
   double tol_used = tol_in, res_start = 1.0;
   for (int pass = 0;; ++pass) {
-    schur_residual64(false, U64, 9, xo, phio, r);
+    schur_residual64(false, xo, phio, r);
     LGT_HIP(launch_finalize(kFinResult1, hop_blocks(g, 1), red(), nullptr, 0, 0.0, 0, stream));
     read_results(1);
     st.true_res = std::sqrt(host_result[0] / pp);
