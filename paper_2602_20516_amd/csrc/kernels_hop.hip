@@ -435,22 +435,28 @@ struct EpiResidual {  // r = phi - (self + coef * acc) over both parities, block
 // at 24^3x48 27.9 -> 26.6 and 31.8 -> 30.4; mixed FP32 force at 16^4 5.81 ->
 // 5.28 ms, where the XCD's own L2 holds part of that end).
 // ---------------------------------------------------------------------------
-// A wave's partial hops in its part of the LDS, in the planes of a half field
-// of 64 sites, and an owner's part of them back.
+// A wave's partial hops in LDS: the planes of a half field of 64 sites, which
+// are written and read as vectors of 16 bytes (an array of float2 alone is
+// only aligned to 8).
 template <typename R>
-__device__ __forceinline__ void put_hops(R2<R>* l, int lane, const C<R>* acc) {
+struct alignas(16) HopStrip {
+  R2<R> v[12 * 64];
+};
+// The strip of a wave's hops, and an owner's part of them back.
+template <typename R>
+__device__ __forceinline__ void put_hops(HopStrip<R>& l, int lane, const C<R>* acc) {
   using P = Planes<R, R2<R>>;
 #pragma unroll
   for (int own = 0; own < P::kOwners; ++own) {
     C<R> v[P::NC];
 #pragma unroll
     for (int q = 0; q < P::NC; ++q) v[q] = acc[P::comp(own, q)];
-    P::st(l, 64, own, lane, v);
+    P::st(l.v, 64, own, lane, v);
   }
 }
 template <typename R>
-__device__ __forceinline__ void get_hops(const R2<R>* l, int lane, int own, C<R>* v) {
-  Planes<R, R2<R>>::ld(l, 64, own, lane, v);
+__device__ __forceinline__ void get_hops(const HopStrip<R>& l, int lane, int own, C<R>* v) {
+  Planes<R, R2<R>>::ld(l.v, 64, own, lane, v);
 }
 
 template <typename R, bool DAG, typename Epi, typename In, int NS>
@@ -459,7 +465,7 @@ __global__ __launch_bounds__(256) void k_hop(Geom g, int nbp, int p_fixed, In hi
   static_assert(NS == 64 || NS == 32, "64 or 32 sites per block");
   if (epi.skip()) return;
   using P = typename Epi::P;
-  __shared__ R2<R> lds[4][12][64];
+  __shared__ HopStrip<R> lds[4];
   const int lb = xcd_block(blockIdx.x, gridDim.x, p_fixed == 1);
   const int p = p_fixed >= 0 ? p_fixed : lb / nbp;
   int blk = p_fixed >= 0 ? lb : lb % nbp;
@@ -509,17 +515,17 @@ __global__ __launch_bounds__(256) void k_hop(Geom g, int nbp, int p_fixed, In hi
       }
     }
   }
-  put_hops<R>(&lds[mu][0][0], lane, acc);
+  put_hops(lds[mu], lane, acc);
   __syncthreads();
   double red = 0.0;
   if constexpr (NS == 64) {
     // wave `mu` now owns its part of the components of the 64 sites
     if (mu < P::kOwners) {
       C<R> out[P::NC], b[P::NC];
-      get_hops<R>(&lds[0][0][0], lane, mu, out);
+      get_hops(lds[0], lane, mu, out);
 #pragma unroll
       for (int m = 1; m < 4; ++m) {
-        get_hops<R>(&lds[m][0][0], lane, mu, b);
+        get_hops(lds[m], lane, mu, b);
 #pragma unroll
         for (int i = 0; i < P::NC; ++i) out[i] += b[i];
       }
@@ -539,8 +545,8 @@ __global__ __launch_bounds__(256) void k_hop(Geom g, int nbp, int p_fixed, In hi
     if (own < P::kOwners) {
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
-        get_hops<R>(&lds[m][0][0], site, own, f);
-        get_hops<R>(&lds[m][0][0], 32 + site, own, b);
+        get_hops(lds[m], site, own, f);
+        get_hops(lds[m], 32 + site, own, b);
 #pragma unroll
         for (int i = 0; i < P::NC; ++i) out[i] += f[i] + b[i];
       }
