@@ -521,14 +521,13 @@ __global__ __launch_bounds__(256) void k_hop(Geom g, int nbp, int p_fixed, In hi
   if constexpr (NS == 64) {
     // wave `mu` now owns its part of the components of the 64 sites
     if (mu < P::kOwners) {
-      C<R> out[P::NC], b[P::NC];
+      C<R> out[P::NC], d1[P::NC], d2[P::NC], d3[P::NC];
       get_hops(lds[0], lane, mu, out);
+      get_hops(lds[1], lane, mu, d1);
+      get_hops(lds[2], lane, mu, d2);
+      get_hops(lds[3], lane, mu, d3);
 #pragma unroll
-      for (int m = 1; m < 4; ++m) {
-        get_hops(lds[m], lane, mu, b);
-#pragma unroll
-        for (int i = 0; i < P::NC; ++i) out[i] += b[i];
-      }
+      for (int i = 0; i < P::NC; ++i) out[i] = (out[i] + d1[i]) + (d2[i] + d3[i]);
       if constexpr (!Epi::kPrefetch) {
         if (active) pre = epi.pre(p, cb, mu);
       }
@@ -539,17 +538,17 @@ __global__ __launch_bounds__(256) void k_hop(Geom g, int nbp, int p_fixed, In hi
     const int site = lane & 31;
     const int own = 2 * mu + (lane >> 5);
     const int cbo = blk * 32 + site;
-    C<R> out[P::NC], f[P::NC], b[P::NC];
-#pragma unroll
-    for (int i = 0; i < P::NC; ++i) out[i] = czero<R>();
+    C<R> out[P::NC], f[P::NC], b[P::NC], d[4][P::NC];
     if (own < P::kOwners) {
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
         get_hops(lds[m], site, own, f);
         get_hops(lds[m], 32 + site, own, b);
 #pragma unroll
-        for (int i = 0; i < P::NC; ++i) out[i] += f[i] + b[i];
+        for (int i = 0; i < P::NC; ++i) d[m][i] = f[i] + b[i];
       }
+#pragma unroll
+      for (int i = 0; i < P::NC; ++i) out[i] = (d[0][i] + d[1][i]) + (d[2][i] + d[3][i]);
       if (cbo < g.vh) epi.apply(p, cbo, own, out, red, epi.pre(p, cbo, own));
     }
   }
