@@ -145,12 +145,15 @@ struct LinkIdx {
 // links of direction w there (the four links of a site share most of their
 // staple links), and blocks are numbered XCD-contiguously, so that
 // neighbouring site blocks -- whose staples read each other's links -- run
-// under the same L2.
-__device__ __forceinline__ bool link_of_thread(const Geom& g, LinkIdx& li) {
+// under the same L2.  wave: the wave's index, as a scalar (wave_id) where links
+// are loaded by it; the forward kernel, which loads all of them through
+// per-lane addresses, loses by it (three levels at 20^4 373 and, on another card, 392 us with
+// the scalar, 370 and 381 with threadIdx.x >> 6; at 16^4 150 and 158, 148 and 155).
+__device__ __forceinline__ bool link_of_thread(const Geom& g, LinkIdx& li, int wave) {
   const int lb = xcd_block(blockIdx.x, gridDim.x);
   li.p = lb & 1;
   li.cb = gauge_site_block(lb, gauge_block_order(g), g.L[2]) * 64 + (threadIdx.x & 63);
-  li.mu = wave_id();
+  li.mu = wave;
   if (li.cb >= g.vh) return false;
   cb_coords(g, li.p, li.cb, li.c);
   return true;
@@ -159,7 +162,7 @@ __device__ __forceinline__ bool link_of_thread(const Geom& g, LinkIdx& li) {
 __global__ __launch_bounds__(256) void k_stout_fwd(Geom g, const double2* __restrict__ U, double2* __restrict__ Uo,
                                                    double rho) {
   LinkIdx li;
-  if (!link_of_thread(g, li)) return;
+  if (!link_of_thread(g, li, threadIdx.x >> 6)) return;
   const M3<double> Ux = load_m3<double>(gptr<double>(U, g, li.p, li.mu), g.vs, li.cb);
   const M3<double> A = staple_A(U, g, li.c, li.mu);
   const M3<double> X = mscale(-rho, proj_ta(mmul(Ux, A)));
@@ -170,7 +173,7 @@ __global__ __launch_bounds__(256) void k_stout_adj_a(Geom g, const double2* __re
                                                      const double2* __restrict__ Gp, double rho,
                                                      double2* __restrict__ Q, double2* __restrict__ Gpart) {
   LinkIdx li;
-  if (!link_of_thread(g, li)) return;
+  if (!link_of_thread(g, li, wave_id())) return;
   const int vh = g.vs;
   const M3<double> Ux = load_m3<double>(gptr<double>(U, g, li.p, li.mu), vh, li.cb);
   const M3<double> A = staple_A(U, g, li.c, li.mu);
@@ -211,7 +214,7 @@ __global__ __launch_bounds__(256) void k_stout_adj_b(Geom g, const double2* __re
                                                      const double2* __restrict__ Gpart, double rho,
                                                      double2* __restrict__ Go) {
   LinkIdx li;
-  if (!link_of_thread(g, li)) return;
+  if (!link_of_thread(g, li, wave_id())) return;
   const int a = li.mu, p = li.p;
   const int* y = li.c;
   M3<double> S = mzero();
@@ -250,7 +253,7 @@ __global__ __launch_bounds__(256) void k_grad_to_force(Geom g, const double2* __
                                                        const double2* __restrict__ G, int mode, double dt,
                                                        double2* __restrict__ out) {
   LinkIdx li;
-  if (!link_of_thread(g, li)) return;
+  if (!link_of_thread(g, li, wave_id())) return;
   const int vh = g.vs;
   const M3<double> Gx = load_m3<double>(gptr<double>(G, g, li.p, li.mu), vh, li.cb);
   M3<double> add;
