@@ -484,9 +484,9 @@ LGT_API lgt_status lgt_hop_benchmark_mrhs(lgt_ctx* ctx, const void* U, const voi
  * a small lattice runs twice as many waves.  0 (the default) takes 32 up to
  * 24576 sites per parity and 64 above.  0 also lets the smallest
  * lattices (3072 sites per parity with FP32 vectors, 2048 with FP64) run a CG
- * iteration as two launches of two hops each.  The two shapes add the eight hop
- * terms of a site in different orders, so results may differ by rounding;
- * each is deterministic.  INVALID_ARGUMENT for any other value, and for 32
+ * iteration as two launches of two hops each.  That form and the shapes may
+ * add the eight hop terms of a site in different orders, so results may differ
+ * by rounding; each is deterministic.  INVALID_ARGUMENT for any other value, and for 32
  * on a lattice whose FP64 gauge field is 4 GiB or more (V above 7456540). */
 LGT_API lgt_status lgt_set_hop_block_sites(lgt_ctx* ctx, int32_t sites);
 

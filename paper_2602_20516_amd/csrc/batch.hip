@@ -102,6 +102,11 @@ static BatchWork* batch_work(lgt_ctx* c, int nr) {
 // each, an interruption of the host or the work of another stream now and then
 // made the choice: at 8^4 x 12 hops of 9 to 11 us instead of 6.6, and three
 // lattices solved side by side took 50 ms with G = 3 at 16^4, 44 with 12.)
+// The FP32 form is timed on two-row links also where the solve, or the
+// operator alone, will read full ones: over 4^4 to 16^4 and 2 to 16
+// right-hand sides the choice made so was within 1.5 % of the best on full
+// links; alone on the card the 8 % give away 6 % of a hop at most (10x14x6x18
+// x 3 in FP64, 16 in FP32), mostly nothing.
 static void tune_group_size(lgt_ctx* c, BatchWork* w, int nr, bool f32) {
   if (w->tuned_nr != nr || w->tuned_kind != c->batch_hop_kind) {
     w->G[0] = w->G[1] = 0;

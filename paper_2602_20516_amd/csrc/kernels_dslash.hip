@@ -16,7 +16,9 @@
 // (218 VGPRs: all 42 loads at once take 232 and ran 212 us at 24^3x48 against
 // 197; three waves spill, 397 us).  The four directions meet in the same
 // strips and the block writes its 64 records as one contiguous span.
-// Bound by memory: 637 MB at 24^3x48 in 197 us, 3.2 TB/s (packing, hop and
+// Bound by memory: at 24^3x48 200 us for the 637 MB it cannot do without, of
+// 1.13 GB that it moves (neighbour records read again from beyond the L2), 5.6
+// TB/s, with the L2's return path busy 80 % of the time (packing, hop and
 // unpacking: 454 us); at 4^4, where launches count, 20 -> 11 us a call.
 // (Arrays of native vectors: of double2 structs the compiler kept a part in
 // scratch, 813 us.)

@@ -26,7 +26,11 @@ namespace lgt {
 // (mixed FP32 force 5.27 or 5.51 ms; padded 5.16 to 5.26; rational force 5.25
 // and 5.10 ms).  Planes of more than 16384 sites that are a multiple of 16384
 // are therefore 2112 = 33 * 64 sites further apart (64, 1088 and 4160 measured
-// within 1 %).  Others stay dense: at 24^3x48 (81 * 2^12 sites) the padding
+// within 1 %).  Padded against dense on further lattices of that kind: solves
+// in FP64, FP32 and BF16 and 1 to 12 shifts 1 % faster at 16^3x24 (49152
+// sites), 1.5 to 2 % at 16^3x32, 1 to 2 % at 16^3x48, 2 to 4 % at 32^4; staple
+// force 3 % from 16^3x32 on; slower only one pass of its own, the Schur
+// operator (83 -> 86 us) and the plaquette sum (121 -> 124), at 16^3x32.  Others stay dense: at 24^3x48 (81 * 2^12 sites) the padding
 // gave the FP64 hop 4 % and cost the smearing 0.6 %, and 8x16^3 (16384 sites)
 // lost by it (FP64 solve 4.90 -> 4.99 ms, rational force 3.34 -> 3.42).  A lattice
 // that only fits the 32-bit field offsets without the padding (for 1..16

@@ -310,12 +310,13 @@ hipError_t launch_bilinear_sum(const Geom& g, const double2* U, const BilinearSu
 // so G = -(beta/3) A^dag and F = (beta/6) P[U A].
 // ---------------------------------------------------------------------------
 // The staple force in site-block form (see k_bilinear_sb).  Bound by what the
-// L2 returns to the CU (links come from it at some 20 bytes a clock and CU;
-// 11 to 16 TB/s here, a multiple of what the memory has to deliver): a
-// thread reads 19 links, of which the four waves of the block share U_nu(x)
-// and U_nu(x-nu), the last factors of its staples.  Each of these is loaded
-// once and exchanged through LDS, 14 loads a thread (32^3x64: 1690 -> 1550
-// us, 16^4: 48.2 -> 44.4).  With U_nu(x) alone 1558 and 45.6; three waves a
+// L2 returns to the CU: 22 to 24 bytes a clock and CU, 12 to 13 TB/s, at
+// 24^3x48 and 32^3x64, with the return unit busy 90 to 95 % of the time and
+// the memory delivering a third of it or less.  A thread reads 19 links, of
+// which the four waves of the block share U_nu(x) and U_nu(x-nu), the last
+// factors of its staples.  Each of these is loaded once and exchanged through
+// LDS, 14 loads a thread (in a gauge step at 32^3x64 1690 -> 1550 us, at 16^4
+// 48.2 -> 44.4).  With U_nu(x) alone 1558 and 45.6; three waves a
 // SIMD instead of two, by fewer registers, 1684.  The stout levels, whose
 // exponential needs the registers, lose by the exchange (one level forward at
 // 24^3x48: 480 -> 560 us) and sum their staples thread by thread.

@@ -147,8 +147,9 @@ struct LinkIdx {
 // neighbouring site blocks -- whose staples read each other's links -- run
 // under the same L2.  wave: the wave's index, as a scalar (wave_id) where links
 // are loaded by it; the forward kernel, which loads all of them through
-// per-lane addresses, loses by it (three levels at 20^4 373 and, on another card, 392 us with
-// the scalar, 370 and 381 with threadIdx.x >> 6; at 16^4 150 and 158, 148 and 155).
+// per-lane addresses, loses by it (three levels at 20^4 373 us with the scalar
+// and 370 with threadIdx.x >> 6, on another card 392 and 381; at 16^4 150 and
+// 148, 158 and 155).
 __device__ __forceinline__ bool link_of_thread(const Geom& g, LinkIdx& li, int wave) {
   const int lb = xcd_block(blockIdx.x, gridDim.x);
   li.p = lb & 1;
@@ -206,7 +207,9 @@ __global__ __launch_bounds__(256) void k_stout_adj_a(Geom g, const double2* __re
 // the ten products per m that the terms take with a stored Lambda.  The
 // kernel is bound by what it gathers past the L2 (24^3x48: 64 % of its reads
 // missed there, 10 GB in 1330 us with Lambda and U at every staple neighbour,
-// 1152 bytes a site); Q and U are 832.  One level's adjoint at 24^3x48 2.39 ->
+// 1152 bytes a site); Q and U are 832, 30 % of the reads miss, and the L2's
+// return path bounds it (24 bytes a clock and CU, 13 TB/s; its unit busy 83 %
+// of the time, the memory at 4.2 TB/s).  One level's adjoint at 24^3x48 2.39 ->
 // 1.78 ms, at 32^3x64 6.9 -> 5.3 ms, of which stage A's smaller output is a
 // tenth.
 __global__ __launch_bounds__(256) void k_stout_adj_b(Geom g, const double2* __restrict__ U,
