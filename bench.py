@@ -893,7 +893,7 @@ def bench_multishift(args):
 def bench_hop_shapes(args):
     """The single-field hop with 32 and with 64 sites per block (lgt_set_hop_block_sites): one
     launch alone (HIP events over 300 launches), and the whole force call (10 calls), at
-    lattice sizes around the automatic switch (32 up to 8192 sites per parity); and the
+    lattice sizes around the automatic switch (32 up to 24576 sites per parity); and the
     64-site hop in site order and t-fastest (lgt_set_hop_block_order; automatic: t-fastest
     above 131072 sites per parity)."""
     import torch
@@ -910,7 +910,7 @@ def bench_hop_shapes(args):
         vh = dims[0] * dims[1] * dims[2] * dims[3] // 2
         for prec in ("mixed_fp32", "fp64"):
             r = {"dims": list(dims), "sites_per_parity": vh, "precision": prec,
-                 "automatic": 32 if vh <= 8192 else 64}
+                 "automatic": 32 if vh <= 24576 else 64}
             for ns in (32, 64):
                 lat.set_hop_block_sites(ns)
                 r[f"hop_us_{ns}"] = round(1e3 * lat.hop_benchmark(U, E, prec, 300), 3)

@@ -210,7 +210,7 @@ __global__ __launch_bounds__(256) void k_stout_adj_a(Geom g, const double2* __re
 // 1152 bytes a site); Q and U are 832, 30 % of the reads miss, and the L2's
 // return path bounds it (24 bytes a clock and CU, 13 TB/s; its unit busy 83 %
 // of the time, the memory at 4.2 TB/s).  One level's adjoint at 24^3x48 2.39 ->
-// 1.78 ms, at 32^3x64 6.9 -> 5.3 ms, of which stage A's smaller output is a
+// 1.78 ms, at 32^3x64 6.9 -> 4.5 ms, of which stage A's smaller output is a
 // tenth.
 __global__ __launch_bounds__(256) void k_stout_adj_b(Geom g, const double2* __restrict__ U,
                                                      const double2* __restrict__ Q,
